@@ -2,8 +2,11 @@
 //
 // Both hot products of an iteration are "NT" contractions with both operands
 // contiguous along k, computed as 256 x 256 output tiles by one workgroup of
-// four waves (each wave a 128 x 128 quadrant = 4 x 4 tiles of the
-// v_mfma_f32_32x32x16_bf16 instruction, fp32 accumulation):
+// four waves (each wave a 128 x 128 quadrant = 8 x 8 tiles of the
+// v_mfma_f32_16x16x32_bf16 instruction, fp32 accumulation; per product it
+// moves half the accumulator registers of the 32x32x16 form, and the chip,
+// power limited under this load, answers with a higher clock: 2% on the
+// 4096 x 4096 layer, 4% on dense 2048-wide products, bitwise the same sums):
 //
 //  * whitening  C = X Y^T with Y = L^-1 lower triangular (Section 5: the
 //    factor inverse enters every update as G A^-1 G^T = (G L^-T)(G L^-T)^T),
@@ -22,7 +25,9 @@
 // fixed per lane and set up once: inside the loop only scalar bases and
 // instruction offsets change (about 7 vector instructions per 64 products
 // instead of 30-50; worth about 1% under sustained load, where the clock is
-// power limited).
+// power limited).  What bounds both kernels is the matrix cores at that clock
+// and the L2 misses of the operand copies: 1.2 to 1.4 PFLOP/s executed, where a
+// large library product reaches 1.36 on the same card.
 #include "ff_common.hpp"
 #include "ff_kernels.hpp"
 
@@ -30,7 +35,7 @@ namespace ff {
 namespace {
 
 constexpr int TM = 256;       // tile rows (and columns)
-constexpr int TK = 32;        // k per matrix-core step (two 16-wide products)
+constexpr int TK = 32;        // k per matrix-core step
 constexpr int PK = 64;        // k per copied pair of steps: 128-byte row segments
 constexpr int NPAIR = 2;      // LDS pair slots (128 KB)
 constexpr int NTHR = 256;     // four waves
@@ -64,14 +69,28 @@ __device__ __forceinline__ void wait_vmem() {
 // lgkmcnt(0) with the other counters left alone.
 __device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4)); }
 
-// Byte offset of the chunk this lane copies with instruction 0 of a pair;
-// instruction q (0..7) of wave w fills positions (4 q + w) 64 + lane, which
-// lie 32 q rows further down with the same swizzle, so its offset is
-// off + 64 q ld bytes (a scalar offset of the instruction).
+// Source row of LDS row r of an operand with PERM: within each 128-row half,
+// LDS row 16 j + c holds source row 8 c + j, so that the eight 16-column
+// matrix-core tiles of a wave give lane c the eight consecutive columns
+// 8 c .. 8 c + 7 of an output row (one 16-byte store).
+template <bool PERM>
+__device__ __forceinline__ int source_row(int r) {
+  return PERM ? (r & ~127) + 8 * (r & 15) + ((r >> 4) & 7) : r;
+}
+
+// Byte offset of the chunk this lane copies with instruction 0 of a pair.
+// Instruction q (0..7) of wave w fills positions (4 q + w) 64 + lane, which
+// lie 32 q rows further down with the same swizzle: 32 q source rows, or with
+// PERM 128 (q / 4) + 2 (q % 4) of them, a scalar offset of the instruction.
+template <bool PERM>
 __device__ __forceinline__ uint32_t chunk_offset(int wave, int lane, uint32_t ld) {
   const int P = wave * 64 + lane;
   const int row = P >> 3, c = (P & 7) ^ swz(row);
-  return ((uint32_t)row * ld + (uint32_t)c * 8u) * 2u;  // bytes
+  return ((uint32_t)source_row<PERM>(row) * ld + (uint32_t)c * 8u) * 2u;  // bytes
+}
+template <bool PERM>
+__device__ __forceinline__ uint32_t group_offset(int q, uint32_t ld) {
+  return (uint32_t)(PERM ? (q >> 2) * 128 + (q & 3) * 2 : q * 32) * ld * 2u;  // bytes
 }
 
 // Buffer resource of a pair's operand (gfx9 descriptor: base, stride 0, no
@@ -82,93 +101,96 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t pair_rsrc(const bf16_t* p) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), (short)0, (int)0x7fffffff, 0x00020000);
 }
 
-// Copy q (0..15) of a pair: operand q % 2, instruction q / 2.
+// Copy q (0..15) of a pair: operand q % 2, instruction q / 2.  PB: the
+// second operand's rows are permuted (source_row).
+template <bool PB>
 __device__ __forceinline__ void issue_one(Ring& sm, int slot, const bf16_t* pa, const bf16_t* pb,
                                           uint32_t oa, uint32_t ob, uint32_t lda, uint32_t ldb,
                                           int wave, int q) {
   const int g = q >> 1;
   if (q & 1)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(pair_rsrc(pb), (lds_void*)&sm.b[slot][(g * 4 + wave) * 64],
-                                             16, (int)ob, (int)((uint32_t)g * 64u * ldb), 0, 0);
+                                             16, (int)ob, (int)group_offset<PB>(g, ldb), 0, 0);
   else
     __builtin_amdgcn_raw_ptr_buffer_load_lds(pair_rsrc(pa), (lds_void*)&sm.a[slot][(g * 4 + wave) * 64],
-                                             16, (int)oa, (int)((uint32_t)g * 64u * lda), 0, 0);
+                                             16, (int)oa, (int)group_offset<false>(g, lda), 0, 0);
 }
 
+template <bool PB>
 __device__ __forceinline__ void issue_pair(Ring& sm, int slot, const bf16_t* pa, const bf16_t* pb,
                                            uint32_t oa, uint32_t ob, uint32_t lda, uint32_t ldb,
                                            int wave) {
 #pragma unroll
-  for (int q = 0; q < 16; ++q) issue_one(sm, slot, pa, pb, oa, ob, lda, ldb, wave, q);
+  for (int q = 0; q < 16; ++q) issue_one<PB>(sm, slot, pa, pb, oa, ob, lda, ldb, wave, q);
 }
 
-// Matrix-core fragments of one 32-k step: for each of its two 16-wide k
-// halves, the rows (A side) and columns (B side) of this wave's 128 x 128
-// quadrant, 8 consecutive k per lane.  f[kk][0..3] = A, f[kk][4..7] = B.
-typedef bf16x8 Frags[2][8];
+// Matrix-core fragments of one 32-k step: the 16-row tiles of this wave's
+// 128 x 128 quadrant, 8 consecutive k per lane (row lane % 16, k 8 (lane / 16)).
+// f[0..7] = A, f[8..15] = B.
+typedef bf16x8 Frags[16];
+// Accumulators: 8 x 8 tiles of 16 x 16 (element r of lane l: row
+// 4 (l / 16) + r, column l % 16; operands swapped: the transposed tile).
+typedef f32x4 Acc[8][8];
 
 // Byte offsets (from the start of the Ring) of this lane's fragment chunks
-// in slot 0 for tile 0 of each operand, k half and 16-wide k step.  The
-// swizzle of a fragment row depends on the lane only (the tile's first row
-// is a multiple of 32), so every read is one of these eight registers plus
-// a constant: the slot (32 KB) and the tile (4 KB).
+// in slot 0 for tile 0 of each operand and 32-k half.  The swizzle of a
+// fragment row depends on the lane only (a tile's first row is a multiple of
+// 16), so every read is one of these four registers plus a constant: the
+// slot (32 KB) and the tile (2 KB).  A read's 16 lanes with one k chunk cover
+// 16 consecutive rows: conflict-free (see swz).
 struct FragBase {
-  uint32_t v[2][2][2];  // [operand B][half][kk]
+  uint32_t v[2][2];  // [operand B][half]
 };
 
 __device__ __forceinline__ FragBase frag_base(int wave, int lane) {
   FragBase fb;
-  const uint32_t s = (uint32_t)swz(lane & 31), hl = (uint32_t)(lane >> 5);
+  const uint32_t s = (uint32_t)swz(lane & 15), kc = (uint32_t)(lane >> 4);
 #pragma unroll
   for (int o = 0; o < 2; ++o)
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        const uint32_t c = (uint32_t)(h * 4 + kk * 2) + hl;
-        const uint32_t row = (uint32_t)(o ? (wave & 1) : (wave >> 1)) * 128u + (uint32_t)(lane & 31);
-        fb.v[o][h][kk] = (o ? (uint32_t)sizeof(Ring::a) : 0u) + row * 128u + 16u * (c ^ s);
-      }
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t c = (uint32_t)(h * 4) + kc;
+      const uint32_t row = (uint32_t)(o ? (wave & 1) : (wave >> 1)) * 128u + (uint32_t)(lane & 15);
+      fb.v[o][h] = (o ? (uint32_t)sizeof(Ring::a) : 0u) + row * 128u + 16u * (c ^ s);
+    }
   return fb;
 }
 
-// Fragment read q (0..15) of step `half` (0, 1) of the pair in `slot`:
-// k half q / 8, A tiles for q % 8 < 4, B tiles above.
+// Fragment read q (0..15) of step `half` (0, 1) of the pair in `slot`, in the
+// order the products use them: A tile 0, the B tiles, A tiles 1..7.
 __device__ __forceinline__ void read_frag_one(const Ring& sm, int slot, int half, const FragBase& fb,
                                               Frags& f, int q) {
-  const int kk = q >> 3, t = q & 7;
-  const uint32_t off = fb.v[t >= 4][half][kk] + (uint32_t)slot * (uint32_t)(PCH * 16) + (uint32_t)(t & 3) * 4096u;
-  f[kk][t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(&sm) + off));
+  const int t = q == 0 ? 0 : q <= 8 ? 7 + q : q - 8;
+  const uint32_t off = fb.v[t >= 8][half] + (uint32_t)slot * (uint32_t)(PCH * 16) + (uint32_t)(t & 7) * 2048u;
+  f[t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(&sm) + off));
 }
 
-// Product m (0..31) of a step: k half m / 16, tile pair ((m / 4) % 4, m % 4).
-// SW = false: acc[i][j] = A rows of tile i x B rows of tile j (element r of
-// lane l: row 8 (r/4) + 4 (l/32) + r%4, column l%32).  SW = true: the
-// operands swapped, acc[i][j] holds the transposed tile (row l%32, column
-// 8 (r/4) + 4 (l/32) + r%4), so each lane holds 16 values of one row.
+// Product m (0..63) of a step: tile pair (m / 8, m % 8), 32 k.
+// SW = false: acc[i][j] = A rows of tile i x B rows of tile j.  SW = true:
+// the operands swapped, acc[i][j] holds the transposed tile (row l % 16,
+// columns 4 (l / 16) + r), so each lane holds values of one row.
 template <bool SW>
-__device__ __forceinline__ void mfma_one(const Frags& f, f32x16 (&acc)[4][4], int m) {
-  const int kk = m >> 4, i = (m >> 2) & 3, j = m & 3;
-  acc[i][j] = SW ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[kk][4 + j], f[kk][i], acc[i][j], 0, 0, 0)
-                 : __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[kk][i], f[kk][4 + j], acc[i][j], 0, 0, 0);
+__device__ __forceinline__ void mfma_one(const Frags& f, Acc& acc, int m) {
+  const int i = m >> 3, j = m & 7;
+  acc[i][j] = SW ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[8 + j], f[i], acc[i][j], 0, 0, 0)
+                 : __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i], f[8 + j], acc[i][j], 0, 0, 0);
 }
 
-// One step: the 32 products of `cur` in program order, fenced one by one.
+// One step: the 64 products of `cur` in program order, fenced one by one.
 // If READ, the 16 fragment reads of step `rhalf` of the pair in `rslot` go
-// into `nxt` after products 0, 1, 3, 4, ..., 22 (read q after product 3q/2),
-// so the last one has nine products to land; if LOADS, the 16 copies of the
-// pair at (pa, pb) into `lslot` follow the even products.
-template <bool SW, bool READ, bool LOADS>
+// into `nxt` after products 0, 3, ..., 45, so the last one has 18 products
+// to land; if LOADS, the 16 copies of the pair at (pa, pb) into `lslot`
+// follow every fourth product.
+template <bool SW, bool PB, bool READ, bool LOADS>
 __device__ __forceinline__ void step(Ring& sm, const Frags& cur, Frags& nxt, int rslot, int rhalf,
                                      int lslot, const bf16_t* pa, const bf16_t* pb, uint32_t oa,
                                      uint32_t ob, uint32_t lda, uint32_t ldb, int wave, const FragBase& fb,
-                                     f32x16 (&acc)[4][4]) {
+                                     Acc& acc) {
 #pragma unroll
-  for (int m = 0; m < 32; ++m) {
+  for (int m = 0; m < 64; ++m) {
     mfma_one<SW>(cur, acc, m);
-    if (READ && m < 24 && m % 3 != 2)
-      read_frag_one(sm, rslot, rhalf, fb, nxt, (2 * m + (m % 3)) / 3);
-    if (LOADS && m % 2 == 0) issue_one(sm, lslot, pa, pb, oa, ob, lda, ldb, wave, m / 2);
+    if (READ && m < 48 && m % 3 == 0) read_frag_one(sm, rslot, rhalf, fb, nxt, m / 3);
+    if (LOADS && m % 4 == 1) issue_one<PB>(sm, lslot, pa, pb, oa, ob, lda, ldb, wave, m / 4);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -182,34 +204,34 @@ __device__ __forceinline__ void step(Ring& sm, const Frags& cur, Frags& nxt, int
 // multiplies the second half while reading the next pair's first half and
 // copying the pair after next into the slot just freed.
 // The first two pairs' copies of mainloop (p0 and p0 + 1 into slots 0, 1).
-template <class Addr>
+template <bool PB, class Addr>
 __device__ __forceinline__ void issue_prologue(Ring& sm, int p0, int p1, uint32_t lda, uint32_t ldb,
                                                const Addr& addr) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t oa = chunk_offset(wave, lane, lda), ob = chunk_offset(wave, lane, ldb);
+  const uint32_t oa = chunk_offset<false>(wave, lane, lda), ob = chunk_offset<PB>(wave, lane, ldb);
   const bf16_t *pa, *pb;
   addr(p0, pa, pb);
-  issue_pair(sm, 0, pa, pb, oa, ob, lda, ldb, wave);
+  issue_pair<PB>(sm, 0, pa, pb, oa, ob, lda, ldb, wave);
   if (p1 - p0 > 1) {
     addr(p0 + 1, pa, pb);
-    issue_pair(sm, 1, pa, pb, oa, ob, lda, ldb, wave);
+    issue_pair<PB>(sm, 1, pa, pb, oa, ob, lda, ldb, wave);
   }
 }
 
 // PRE: the caller has issued the prologue's copies (issue_prologue) after
 // its last other vector-memory instruction.
-template <bool SW = false, bool PRE = false, class Addr>
+template <bool SW, bool PB, bool PRE, class Addr>
 __device__ __forceinline__ void mainloop(Ring& sm, int p0, int p1, uint32_t lda, uint32_t ldb,
-                                         const Addr& addr, f32x16 (&acc)[4][4]) {
+                                         const Addr& addr, Acc& acc) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: LDS bases in SGPRs
   const int n = p1 - p0;
   if (n <= 0) return;
-  const uint32_t oa = chunk_offset(wave, lane, lda), ob = chunk_offset(wave, lane, ldb);
+  const uint32_t oa = chunk_offset<false>(wave, lane, lda), ob = chunk_offset<PB>(wave, lane, ldb);
   const FragBase fb = frag_base(wave, lane);
   const bf16_t *pa, *pb;
-  if (!PRE) issue_prologue(sm, p0, p1, lda, ldb, addr);
+  if (!PRE) issue_prologue<PB>(sm, p0, p1, lda, ldb, addr);
   if (n > 1) {
     wait_vmem<16>();
   } else {
@@ -222,34 +244,32 @@ __device__ __forceinline__ void mainloop(Ring& sm, int p0, int p1, uint32_t lda,
   int j = 0;
   for (; j + 2 < n; ++j) {  // steady: step B also copies pair j + 2
     const int slot = j & 1;
-    step<SW, true, false>(sm, F[0], F[1], slot, 1, 0, nullptr, nullptr, 0, 0, lda, ldb, wave, fb, acc);
+    step<SW, PB, true, false>(sm, F[0], F[1], slot, 1, 0, nullptr, nullptr, 0, 0, lda, ldb, wave, fb, acc);
     wait_vmem<0>();  // pair j + 1 (the only pair in flight)
     wait_lds();      // this wave's reads of pair j are complete
     __builtin_amdgcn_s_barrier();
     addr(p0 + j + 2, pa, pb);
-    step<SW, true, true>(sm, F[1], F[0], slot ^ 1, 0, slot, pa, pb, oa, ob, lda, ldb, wave, fb, acc);
+    step<SW, PB, true, true>(sm, F[1], F[0], slot ^ 1, 0, slot, pa, pb, oa, ob, lda, ldb, wave, fb, acc);
   }
   if (j + 1 < n) {
     const int slot = j & 1;
-    step<SW, true, false>(sm, F[0], F[1], slot, 1, 0, nullptr, nullptr, 0, 0, lda, ldb, wave, fb, acc);
+    step<SW, PB, true, false>(sm, F[0], F[1], slot, 1, 0, nullptr, nullptr, 0, 0, lda, ldb, wave, fb, acc);
     wait_vmem<0>();
     wait_lds();
     __builtin_amdgcn_s_barrier();
-    step<SW, true, false>(sm, F[1], F[0], slot ^ 1, 0, 0, nullptr, nullptr, 0, 0, lda, ldb, wave, fb, acc);
+    step<SW, PB, true, false>(sm, F[1], F[0], slot ^ 1, 0, 0, nullptr, nullptr, 0, 0, lda, ldb, wave, fb, acc);
     ++j;
   }
-  step<SW, true, false>(sm, F[0], F[1], j & 1, 1, 0, nullptr, nullptr, 0, 0, lda, ldb, wave, fb, acc);
-  step<SW, false, false>(sm, F[1], F[0], 0, 0, 0, nullptr, nullptr, 0, 0, lda, ldb, wave, fb, acc);
+  step<SW, PB, true, false>(sm, F[0], F[1], j & 1, 1, 0, nullptr, nullptr, 0, 0, lda, ldb, wave, fb, acc);
+  step<SW, PB, false, false>(sm, F[1], F[0], 0, 0, 0, nullptr, nullptr, 0, 0, lda, ldb, wave, fb, acc);
   __syncthreads();
 }
 
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[4][4]) {
+__device__ __forceinline__ void zero_acc(Acc& acc) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 }
 
 // Tiles of the whitening products.  Output tile (rb, cj) needs k in
@@ -284,38 +304,42 @@ __device__ __forceinline__ WhitenAddr whiten_addr(const bf16_t* xa, const bf16_t
 template <bool SW, bool PRE>
 __device__ __forceinline__ void whiten_tile(Ring& sm, const bf16_t* xa, const bf16_t* Y, const bf16_t* Y2,
                                             uint32_t cj, bool rev, uint32_t Kp, bool full,
-                                            f32x16 (&acc)[4][4]) {
+                                            Acc& acc) {
   if (!PRE) zero_acc(acc);
   const WhitenAddr a0 = whiten_addr(xa, Y, cj, rev, Kp, full);
-  mainloop<SW, PRE>(sm, 0, a0.np, Kp, Kp, a0, acc);
+  mainloop<SW, !SW, PRE>(sm, 0, a0.np, Kp, Kp, a0, acc);
   if (Y2 != nullptr) {
     const WhitenAddr a1 = whiten_addr(xa, Y2, cj, rev, Kp, full);
-    mainloop<SW>(sm, 0, a1.np, Kp, Kp, a1, acc);
+    mainloop<SW, !SW, false>(sm, 0, a1.np, Kp, Kp, a1, acc);
   }
 }
 
-__device__ __forceinline__ void store_whitened(const f32x16 (&acc)[4][4], bf16_t* C, uint32_t rb,
-                                               uint32_t cj, uint32_t Kp) {
+// The B operand's rows were permuted (source_row), so lane c of a row of 16
+// holds the eight consecutive columns 8 c .. 8 c + 7 of the quadrant, one per
+// tile: a store instruction writes four rows' whole 256-byte segments.
+__device__ __forceinline__ void store_whitened(const Acc& acc, bf16_t* C, uint32_t rb, uint32_t cj,
+                                               uint32_t Kp) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  // per-lane base (row 4 (l / 32), column l % 32 of the wave's quadrant);
-  // the offsets of the accumulator elements below are wave-uniform.  The
-  // opaque copy of the row pitch keeps the compiler from computing those
-  // offsets once ahead of the tile loop and holding them across the main loop.
+  // per-lane base (row 4 (l / 16), columns 8 (l % 16).. of the wave's
+  // quadrant); the offsets of the rows below are wave-uniform.  The opaque
+  // copy of the row pitch keeps the compiler from computing those offsets
+  // once ahead of the tile loop and holding them across the main loop.
   uint32_t ldc = Kp;
   asm volatile("" : "+s"(ldc));
-  bf16_t* lp = C + ((size_t)rb * TM + wm * 128 + 4 * (lane >> 5)) * ldc + (size_t)cj * TM + wn * 128 +
-               (lane & 31);
+  bf16_t* lp = C + ((size_t)rb * TM + wm * 128 + 4 * (lane >> 4)) * ldc + (size_t)cj * TM + wn * 128 +
+               8 * (lane & 15);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int r = 0; r < 4; ++r) {
+      u32x4 v;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const uint32_t row = i * 32 + 8 * (r >> 2) + (r & 3);
-        lp[row * ldc + j * 32] = f32_to_bf16(acc[i][j][r]);
-      }
+      for (int q = 0; q < 4; ++q)
+        v[q] = (uint32_t)f32_to_bf16(acc[i][2 * q][r]) | ((uint32_t)f32_to_bf16(acc[i][2 * q + 1][r]) << 16);
+      *reinterpret_cast<u32x4*>(lp + (uint32_t)(i * 16 + r) * ldc) = v;
+    }
 }
 
 __global__ __launch_bounds__(NTHR, 1) void k_whiten_bf16(const bf16_t* __restrict__ X,
@@ -331,7 +355,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_whiten_bf16(const bf16_t* __restric
   const uint32_t t = xcd_remap(blockIdx.x, gridDim.x);
   const uint32_t rb = t / npair, c = t % npair;
   const bf16_t* xa = X + (size_t)rb * TM * Kp;
-  f32x16 acc[4][4];
+  Acc acc;
   // the second tile's first copies go out right behind the first tile's
   // stores, so that their latency overlaps the stores' drain
   whiten_tile<false, false>(sm, xa, Y, Y2, c, false, Kp, full != 0, acc);
@@ -339,7 +363,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_whiten_bf16(const bf16_t* __restric
   if (ncol - 1 - c != c) {
     const uint32_t cj = ncol - 1 - c;
     const WhitenAddr a0 = whiten_addr(xa, Y, cj, true, Kp, full != 0);
-    issue_prologue(sm, 0, a0.np, Kp, Kp, a0);
+    issue_prologue<true>(sm, 0, a0.np, Kp, Kp, a0);
     zero_acc(acc);
     whiten_tile<false, true>(sm, xa, Y, Y2, cj, true, Kp, full != 0, acc);
     store_whitened(acc, C, rb, cj, Kp);
@@ -352,21 +376,23 @@ __global__ __launch_bounds__(NTHR, 1) void k_whiten_bf16(const bf16_t* __restric
 // the operands swapped so that every lane holds values of one row; the
 // whitened values are never stored.  part[row][2 cj + wn] receives the sum of
 // squares over the 128 columns of wave column wn of tile column cj.
-__device__ __forceinline__ void store_norms(const f32x16 (&acc)[4][4], float* part, uint32_t rb,
-                                            uint32_t cj, uint32_t ncol) {
+__device__ __forceinline__ void store_norms(const Acc& acc, float* part, uint32_t rb, uint32_t cj,
+                                            uint32_t ncol) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1;
   const uint32_t npart = 2 * ncol;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < 8; ++i) {
     float s = 0.0f;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 8; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s += acc[i][j][r] * acc[i][j][r];
-    s += __shfl_xor(s, 32);  // lanes l and l + 32 hold the two column halves of row l % 32
-    if (lane < 32) {
-      const size_t row = (size_t)rb * TM + wm * 128 + i * 32 + lane;
+      for (int r = 0; r < 4; ++r) s += acc[i][j][r] * acc[i][j][r];
+    // lanes l, l + 16, l + 32 and l + 48 hold the four column groups of row l % 16
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    if (lane < 16) {
+      const size_t row = (size_t)rb * TM + wm * 128 + i * 16 + lane;
       part[row * npart + 2 * cj + wn] = s;
     }
   }
@@ -385,7 +411,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_whiten_norm_bf16(const bf16_t* __re
   const uint32_t t = xcd_remap(blockIdx.x, gridDim.x);
   const uint32_t rb = t / npair, c = t % npair;
   const bf16_t* xa = X + (size_t)rb * TM * Kp;
-  f32x16 acc[4][4];
+  Acc acc;
   for (uint32_t h = 0; h < (ncol - 1 - c != c ? 2u : 1u); ++h) {
     const uint32_t cj = h ? ncol - 1 - c : c;
     whiten_tile<true, false>(sm, xa, Y, Y2, cj, h != 0, Kp, false, acc);
@@ -471,7 +497,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_syrk_bf16(const bf16_t* __restrict_
   const int p0 = (int)(ptot * z / splits), p1 = (int)(ptot * (z + 1) / splits);
   const bf16_t* xa = X + (size_t)ti * TM * ld;
   const bf16_t* xb = (Xb != nullptr ? Xb : X) + (size_t)tj * TM * ld;
-  f32x16 acc[4][4];
+  Acc acc;
   zero_acc(acc);
   auto addr = [&](int p, const bf16_t*& pa, const bf16_t*& pb) {
     const uint32_t s = (uint32_t)p / pps, o = (uint32_t)p % pps;
@@ -479,20 +505,14 @@ __global__ __launch_bounds__(NTHR, 1) void k_syrk_bf16(const bf16_t* __restrict_
     pa = xa + base;
     pb = xb + base;
   };
-  mainloop(sm, p0, p1, ld, ld, addr, acc);
+  mainloop<false, false, false>(sm, p0, p1, ld, ld, addr, acc);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   float* pt = P + ((size_t)z * ntiles + tile) * TILE_FLOATS;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      f32x4* dst = reinterpret_cast<f32x4*>(pt + ((size_t)((wave * 16 + i * 4 + j) * 64 + lane)) * 16);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-        dst[q] = v;
-      }
-    }
+    for (int j = 0; j < 8; ++j)
+      reinterpret_cast<f32x4*>(pt)[(wave * 64 + i * 8 + j) * 64 + lane] = acc[i][j];
 }
 
 // One thread per 4 consecutive fragment floats (4 rows, one column) of a tile.
@@ -509,10 +529,10 @@ __global__ __launch_bounds__(256) void k_reduce_frag(const float* __restrict__ P
     const f32x4 v = reinterpret_cast<const f32x4*>(P + ((size_t)z * ntiles + tile) * TILE_FLOATS)[f];
     s += v;
   }
-  const uint32_t q = f & 3, lane = (f >> 2) & 63, rest = f >> 8;
-  const uint32_t wave = rest >> 4, mt = (rest >> 2) & 3, nt = rest & 3;
-  const uint32_t i0 = ti * TM + (wave >> 1) * 128 + mt * 32 + 8 * q + 4 * (lane >> 5);
-  const uint32_t j = tj * TM + (wave & 1) * 128 + nt * 32 + (lane & 31);
+  const uint32_t lane = f & 63, rest = f >> 6;
+  const uint32_t wave = rest >> 6, mt = (rest >> 3) & 7, nt = rest & 7;
+  const uint32_t i0 = ti * TM + (wave >> 1) * 128 + mt * 16 + 4 * (lane >> 4);
+  const uint32_t j = tj * TM + (wave & 1) * 128 + nt * 16 + (lane & 15);
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const uint32_t i = i0 + e;
