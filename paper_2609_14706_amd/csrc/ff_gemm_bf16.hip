@@ -280,38 +280,56 @@ __device__ __forceinline__ void zero_acc(Acc& acc) {
 // workgroup all pairs of a row block sit at k slice t or 8 (ncol + 1) - 1 - t,
 // so the workgroups that run together on an XCD (consecutive pairs of a few
 // row blocks) stay in step and share their operand slices in its L2.
-// Operand addresses of pair p of tile column cj (pass 0: Y, pass 1: Y2).
+//
+// With the low parts (Y2) one run of pairs goes through all k of Y, then
+// through all k of Y2.
+// Operand addresses of pair p of tile column cj.
 struct WhitenAddr {
   const bf16_t* xa;
   const bf16_t* yb;
-  int np;
+  const bf16_t* yb2;  // null: one pass
+  int nk;             // k pairs
   bool rev;
+  __device__ __forceinline__ int pairs() const { return yb2 != nullptr ? 2 * nk : nk; }
   __device__ __forceinline__ void operator()(int p, const bf16_t*& pa, const bf16_t*& pb) const {
-    const int k = rev ? np - 1 - p : p;
+    const bool second = p >= nk;
+    const int q = second ? p - nk : p;
+    // uniform (as p is): the bases below have to stay in scalar registers
+    const int k = __builtin_amdgcn_readfirstlane(rev ? nk - 1 - q : q);
     pa = xa + k * PK;
-    pb = yb + k * PK;
+    pb = (second ? yb2 : yb) + k * PK;
   }
 };
 
-__device__ __forceinline__ WhitenAddr whiten_addr(const bf16_t* xa, const bf16_t* Y, uint32_t cj,
-                                                  bool rev, uint32_t Kp, bool full) {
-  const int np = (int)((full ? Kp / TM : cj + 1) * (TM / PK));
-  return WhitenAddr{xa, Y + (size_t)cj * TM * Kp, np, rev};
+__device__ __forceinline__ WhitenAddr whiten_addr(const bf16_t* xa, const bf16_t* Y, const bf16_t* Y2,
+                                                  uint32_t cj, bool rev, uint32_t Kp, bool full) {
+  const int nk = (int)((full ? Kp / TM : cj + 1) * (TM / PK));
+  const size_t off = (size_t)cj * TM * Kp;
+  return WhitenAddr{xa, Y + off, Y2 != nullptr ? Y2 + off : nullptr, nk, rev};
 }
 
-// acc = X Y^T (+ X Y2^T) over tile column cj; PRE: the first pass's prologue
-// copies are issued and acc is zero already.
-template <bool SW, bool PRE>
-__device__ __forceinline__ void whiten_tile(Ring& sm, const bf16_t* xa, const bf16_t* Y, const bf16_t* Y2,
-                                            uint32_t cj, bool rev, uint32_t Kp, bool full,
-                                            Acc& acc) {
-  if (!PRE) zero_acc(acc);
-  const WhitenAddr a0 = whiten_addr(xa, Y, cj, rev, Kp, full);
-  mainloop<SW, !SW, PRE>(sm, 0, a0.np, Kp, Kp, a0, acc);
-  if (Y2 != nullptr) {
-    const WhitenAddr a1 = whiten_addr(xa, Y2, cj, rev, Kp, full);
-    mainloop<SW, !SW, false>(sm, 0, a1.np, Kp, Kp, a1, acc);
-  }
+// Workgroup t of an XCD's consecutive ones -> row block rb and column pair c.
+// The 32 workgroups that run together on an XCD take 4 row blocks x 8 column
+// pairs: 12 operand tiles a k step for 64 tile reads, where 32 column pairs
+// of one row block (wide operands: ncol / 2 pairs >= 32) read 33.  Up to
+// Kp = 4096 (8 pairs) it is four whole row blocks either way.  Half step of
+// the 8192 x 28672 layer (two passes): 598 -> 544 ms.
+constexpr uint32_t WGR = 4, WGC = 8;
+// Automatic split with both factors' flags clear.  Made uniform for the
+// compiler: the copies' operand base depends on it, and a base it cannot
+// prove uniform turns every copy into a loop over the lanes' values.
+__device__ __forceinline__ bool one_pass(const int* use2, const int* use2b) {
+  if (use2 == nullptr) return false;
+  const int f = *use2 | (use2b != nullptr ? *use2b : 0);
+  return __builtin_amdgcn_readfirstlane(f) == 0;
+}
+__device__ __forceinline__ void whiten_item(uint32_t t, uint32_t nrb, uint32_t npair, uint32_t& rb,
+                                            uint32_t& c) {
+  const uint32_t strip = t / (WGR * npair), u = t - strip * WGR * npair;
+  const uint32_t r = min(WGR, nrb - strip * WGR);  // row blocks of this strip
+  const uint32_t cg = u / (WGC * r), v = u - cg * WGC * r;
+  rb = strip * WGR + v % r;
+  c = cg * WGC + v / r;
 }
 
 // The B operand's rows were permuted (source_row), so lane c of a row of 16
@@ -349,23 +367,25 @@ __global__ __launch_bounds__(NTHR, 1) void k_whiten_bf16(const bf16_t* __restric
                                                          bf16_t* __restrict__ C, uint32_t Kp,
                                                          uint32_t full, const int* st) {
   if (ff_halted(st)) return;
-  if (use2 != nullptr && *use2 == 0 && (use2b == nullptr || *use2b == 0)) Y2 = nullptr;  // one pass
+  if (one_pass(use2, use2b)) Y2 = nullptr;
   __shared__ Ring sm;
   const uint32_t ncol = Kp / TM, npair = (ncol + 1) / 2;
-  const uint32_t t = xcd_remap(blockIdx.x, gridDim.x);
-  const uint32_t rb = t / npair, c = t % npair;
+  uint32_t rb, c;
+  whiten_item(xcd_remap(blockIdx.x, gridDim.x), gridDim.x / npair, npair, rb, c);
   const bf16_t* xa = X + (size_t)rb * TM * Kp;
   Acc acc;
-  // the second tile's first copies go out right behind the first tile's
-  // stores, so that their latency overlaps the stores' drain
-  whiten_tile<false, false>(sm, xa, Y, Y2, c, false, Kp, full != 0, acc);
+  zero_acc(acc);
+  const WhitenAddr a0 = whiten_addr(xa, Y, Y2, c, false, Kp, full != 0);
+  mainloop<false, true, false>(sm, 0, a0.pairs(), Kp, Kp, a0, acc);
   store_whitened(acc, C, rb, c, Kp);
   if (ncol - 1 - c != c) {
+    // the second tile's first copies go out right behind the first tile's
+    // stores, so that their latency overlaps the stores' drain
     const uint32_t cj = ncol - 1 - c;
-    const WhitenAddr a0 = whiten_addr(xa, Y, cj, true, Kp, full != 0);
-    issue_prologue<true>(sm, 0, a0.np, Kp, Kp, a0);
+    const WhitenAddr a1 = whiten_addr(xa, Y, Y2, cj, true, Kp, full != 0);
+    issue_prologue<true>(sm, 0, a1.pairs(), Kp, Kp, a1);
     zero_acc(acc);
-    whiten_tile<false, true>(sm, xa, Y, Y2, cj, true, Kp, full != 0, acc);
+    mainloop<false, true, true>(sm, 0, a1.pairs(), Kp, Kp, a1, acc);
     store_whitened(acc, C, rb, cj, Kp);
   }
 }
@@ -405,16 +425,23 @@ __global__ __launch_bounds__(NTHR, 1) void k_whiten_norm_bf16(const bf16_t* __re
                                                               float* __restrict__ part, uint32_t Kp,
                                                               const int* st) {
   if (ff_halted(st)) return;
-  if (use2 != nullptr && *use2 == 0 && (use2b == nullptr || *use2b == 0)) Y2 = nullptr;  // one pass
+  if (one_pass(use2, use2b)) Y2 = nullptr;
   __shared__ Ring sm;
   const uint32_t ncol = Kp / TM, npair = (ncol + 1) / 2;
-  const uint32_t t = xcd_remap(blockIdx.x, gridDim.x);
-  const uint32_t rb = t / npair, c = t % npair;
+  uint32_t rb, c;
+  whiten_item(xcd_remap(blockIdx.x, gridDim.x), gridDim.x / npair, npair, rb, c);
   const bf16_t* xa = X + (size_t)rb * TM * Kp;
   Acc acc;
-  for (uint32_t h = 0; h < (ncol - 1 - c != c ? 2u : 1u); ++h) {
-    const uint32_t cj = h ? ncol - 1 - c : c;
-    whiten_tile<true, false>(sm, xa, Y, Y2, cj, h != 0, Kp, false, acc);
+  zero_acc(acc);
+  const WhitenAddr a0 = whiten_addr(xa, Y, Y2, c, false, Kp, false);
+  mainloop<true, false, false>(sm, 0, a0.pairs(), Kp, Kp, a0, acc);
+  store_norms(acc, part, rb, c, ncol);
+  if (ncol - 1 - c != c) {
+    const uint32_t cj = ncol - 1 - c;
+    const WhitenAddr a1 = whiten_addr(xa, Y, Y2, cj, true, Kp, false);
+    issue_prologue<false>(sm, 0, a1.pairs(), Kp, Kp, a1);
+    zero_acc(acc);
+    mainloop<true, false, true>(sm, 0, a1.pairs(), Kp, Kp, a1, acc);
     store_norms(acc, part, rb, cj, ncol);
   }
 }
