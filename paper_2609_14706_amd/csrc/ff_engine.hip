@@ -122,7 +122,22 @@ int choose_splits_f32(int64_t dim_p, int64_t K) {
   const int64_t T = (dim_p + 127) / 128, tiles = T * (T + 1) / 2;
   int64_t S = std::max<int64_t>(1, 512 / tiles);
   S = std::min<int64_t>(S, std::max<int64_t>(1, K / 256));
-  return (int)std::min<int64_t>(S, 256);
+  S = std::min<int64_t>(S, 256);
+  if (T * T * S < 256) return (int)S;  // 64 x 64 tiles (launch_gemm_f32)
+  // 256 x 128 tiles, one workgroup per CU: of the splits up to that many (the
+  // partial outputs' memory), the one with the least rounds of 256 workgroups
+  // times slices of 32 k; 14 -> 12 splits of a 1024-wide product over 32768 k
+  // are one round instead of two
+  int64_t wide = 0, best = INT64_MAX, bestS = S;
+  for (int64_t b = 0; b < (dim_p + 255) / 256; ++b) wide += std::min<int64_t>(2 * (b + 1), T);
+  for (int64_t s = S; s >= 1 && T * T * s >= 256; --s) {
+    const int64_t t = (wide * s + 255) / 256 * ((K + 32 * s - 1) / (32 * s) + 4);
+    if (t < best) {
+      best = t;
+      bestS = s;
+    }
+  }
+  return (int)bestS;
 }
 
 ff_status validate_shape(const ff_config* c) {
@@ -313,11 +328,13 @@ ff_status side_streams(Side& s) {
   return FF_OK;
 }
 
+constexpr int64_t kTwoLevel = 6144;  // wider factors go in outer panels (see chol_blocked)
+
 // Off-diagonal blocks of L^-1 for the node [o, o + sz) of the leaf tree, on
 // stream st, in two products: P1, T^T = (L21 Li11)^T, parked in the node's
 // block above the diagonal of s.L, needs the left half done (its inverse and
 // the panels below it); P2, Li21 = -Li22 T, needs the right half's inverse
-// too.  64 x 64 tiles below 2048 rows: with one operand triangular, 128 x 128
+// too.  64 x 64 tiles below 2048 rows: with one operand triangular, larger
 // tiles leave a few long workgroups to finish alone.
 struct TreeNode {
   int64_t hh, r;
@@ -340,7 +357,10 @@ TreeNode tree_node(Side& s, int64_t o, int64_t sz) {
 
 GemmF32 tree_gemm(ff_handle_s* h, Side& s, const TreeNode& t) {
   GemmF32 g{};
-  g.tile = t.hh < 2048 ? 64 : 0;
+  // wide nodes of wide factors: 256 x 128 tiles of three-part products; a
+  // one-level factor's few wide nodes run beside its steps (64 x 64 tiles: 4096
+  // factor 2.03 ms either way)
+  g.tile = s.dim <= kTwoLevel || t.hh < 2048 ? 64 : 0;
   g.lda = g.ldb = g.ldc = s.dim;
   g.kseg = INT64_MAX / 4;
   g.ksplit = 1;
@@ -420,7 +440,6 @@ ff_status inverse_p1_split(ff_handle_s* h, Side& s, int64_t o, int64_t sz, int64
 // after the last leaf is the factorisation's tail.  The upper triangle of
 // s.L is scratch.
 constexpr int64_t kInvEvery = 8;
-constexpr int64_t kTwoLevel = 6144;
 constexpr int64_t kOuter = 2048;
 
 ff_status chol_blocked(ff_handle_s* h, Side& s, int iteration) {

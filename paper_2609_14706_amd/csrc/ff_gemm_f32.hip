@@ -1,15 +1,13 @@
 // General fp32 product on the fp32 matrix cores (v_mfma_f32_32x32x2_f32).
 //
-// Used wherever the iteration needs fp32 products: the blocked Cholesky and
-// triangular inverse of the factors, the whole fp32 sample path (whitening
-// and symmetric product), and the Kronecker application.  128 x 128 output
-// tiles, four waves of 64 x 64 (2 x 2 matrix-core tiles), 32-wide k slices
-// staged through double-buffered LDS; when fewer than 256 such tiles would be
-// launched, 64 x 64 tiles (one 32 x 32 matrix-core tile per wave) with 64-wide
-// k slices.  Any shape and either operand
-// transpose; k ranges can be clipped to the non-zero triangle of a
-// triangular operand, k can run over segments (the stacked samples), and k
-// can be split over the grid into partial outputs.  When every operand is
+// The smaller fp32 products: the tree of the triangular inverse of a factor,
+// small fp32 layers.  64 x 64 output tiles, four waves of one 32 x 32
+// matrix-core tile, 64-wide k slices staged through double-buffered LDS (such
+// products are latency bound: few, large slices).  Products that give the
+// GPU 256 tiles of 128 x 128 or more go to ff_gemm_split.hip.  Any shape and
+// either operand transpose; k ranges can be clipped to the non-zero triangle
+// of a triangular operand, k can run over segments (the stacked samples), and
+// k can be split over the grid into partial outputs.  When every operand is
 // 16-byte aligned with leading dimensions divisible by 4, global loads are
 // 16-byte vectors (edge vectors fall back to element loads).
 #include "ff_common.hpp"
@@ -18,14 +16,11 @@
 namespace ff {
 namespace {
 
-constexpr int LDPMAX = 128 + 4;
 // k range per workgroup above which products use two-level accumulation
 constexpr int64_t kDeepK = 16384;
 
-// k per LDS slice: 32 for 128 x 128 tiles, 64 for 64 x 64 tiles (the small
-// products of the factorisation are latency bound: fewer, larger slices).
-template <int BT>
-constexpr int slice_k() { return BT == 128 ? 32 : 64; }
+constexpr int BT = 64;  // tile rows and columns
+constexpr int BK = 64;  // k per LDS slice
 
 // Offset of k in a k axis made of segments of kseg, seg apart (kseg == 0:
 // one contiguous axis, no division).
@@ -33,14 +28,13 @@ __device__ __forceinline__ int64_t seg_off(int64_t k, int64_t kseg, int64_t seg)
   return kseg ? (k / kseg) * seg + (k % kseg) : k;
 }
 
-// One operand slice: 128 "outer" indices (rows of op(A) or columns of op(B))
-// x 16 k.  KMAJ: the operand is contiguous along k (element (o, k) at
+// One operand slice: 64 "outer" indices (rows of op(A) or columns of op(B))
+// x 64 k.  KMAJ: the operand is contiguous along k (element (o, k) at
 // P[o * ld + koff(k)]); otherwise contiguous along o (at P[koff(k) * ld + o]).
 // Each thread fetches NQ 4-element groups; slice[k][o] is written to LDS.
 // FAST: the whole slice is in bounds and 16-byte vectors can be used.
-template <int BT, bool KMAJ, bool FAST>
+template <bool KMAJ, bool FAST>
 struct SliceLoader {
-  static constexpr int BK = slice_k<BT>();
   static constexpr int NQ = BT * BK / 4 / 256;  // 4-element groups per thread
   static constexpr int OQ = BT / 4;             // 4-element groups per k row (non-k-major)
   f32x4 v[NQ];
@@ -87,25 +81,23 @@ struct SliceLoader {
   }
 };
 
-template <int BT>
 struct TileLDS {
-  float a[2][slice_k<BT>()][BT + 4];
-  float b[2][slice_k<BT>()][BT + 4];
+  float a[2][BK][BT + 4];
+  float b[2][BK][BT + 4];
 };
 
-// acc += op(A)[i0.., klo..khi) op(B)[klo..khi), j0..) for one BT x BT tile
-// (each wave a (BT/2) x (BT/2) quadrant of MT x MT 32 x 32 matrix-core tiles).
+// acc += op(A)[i0.., klo..khi) op(B)[klo..khi), j0..) for one tile (each wave
+// one 32 x 32 quadrant).
 // DEEP: two-level accumulation (see below), for long k ranges only: its
 // second set of accumulators halves the waves a CU can hold.
-template <int BT, bool AK, bool BKM, bool FAST, bool DEEP>
+template <bool AK, bool BKM, bool FAST, bool DEEP>
 __device__ __forceinline__ void tile_product(const GemmF32& p, const float* A, const float* B,
                                              int64_t i0, int64_t j0, int64_t klo, int64_t khi,
-                                             TileLDS<BT>& sm, f32x16 (&acc)[BT / 64][BT / 64]) {
-  constexpr int MT = BT / 64, BK = slice_k<BT>();
+                                             TileLDS& sm, f32x16& acc) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1;
-  SliceLoader<BT, AK, FAST> la;
-  SliceLoader<BT, BKM, FAST> lb;
+  SliceLoader<AK, FAST> la;
+  SliceLoader<BKM, FAST> lb;
   la.load(A, p.lda, i0, p.M, klo, khi, p.kseg, p.segA, tid);
   lb.load(B, p.ldb, j0, p.N, klo, khi, p.kseg, p.segB, tid);
   la.store(sm.a[0], tid);
@@ -116,13 +108,9 @@ __device__ __forceinline__ void tile_product(const GemmF32& p, const float* A, c
   // stacked samples, hundreds of thousands deep) thus round each output
   // element about CHUNK * BK / 2 + K / (CHUNK * BK) times instead of K / 2.
   constexpr int CHUNK = 8;
-  f32x16 loc[MT][MT];
+  f32x16 loc;
 #pragma unroll
-  for (int a = 0; a < MT; ++a)
-#pragma unroll
-    for (int b = 0; b < MT; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) loc[a][b][r] = 0.0f;
+  for (int r = 0; r < 16; ++r) loc[r] = 0.0f;
   int cnt = 0;
   int cur = 0;
   for (int64_t k0 = klo; k0 < khi; k0 += BK) {
@@ -133,42 +121,24 @@ __device__ __forceinline__ void tile_product(const GemmF32& p, const float* A, c
     }
     __builtin_amdgcn_sched_barrier(0);
     // operands of k-step s + 1 are read while the products of step s run
-    float fa[2][MT], fb[2][MT];
-#pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      fa[0][t] = sm.a[cur][lane >> 5][wm * (BT / 2) + t * 32 + (lane & 31)];
-      fb[0][t] = sm.b[cur][lane >> 5][wn * (BT / 2) + t * 32 + (lane & 31)];
-    }
+    float fa[2], fb[2];
+    fa[0] = sm.a[cur][lane >> 5][wm * 32 + (lane & 31)];
+    fb[0] = sm.b[cur][lane >> 5][wn * 32 + (lane & 31)];
 #pragma unroll
     for (int s = 0; s < BK / 2; ++s) {
       if (s + 1 < BK / 2) {
         const int kr = 2 * (s + 1) + (lane >> 5);
-#pragma unroll
-        for (int t = 0; t < MT; ++t) {
-          fa[(s + 1) & 1][t] = sm.a[cur][kr][wm * (BT / 2) + t * 32 + (lane & 31)];
-          fb[(s + 1) & 1][t] = sm.b[cur][kr][wn * (BT / 2) + t * 32 + (lane & 31)];
-        }
+        fa[(s + 1) & 1] = sm.a[cur][kr][wm * 32 + (lane & 31)];
+        fb[(s + 1) & 1] = sm.b[cur][kr][wn * 32 + (lane & 31)];
       }
       __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the products
-#pragma unroll
-      for (int a = 0; a < MT; ++a)
-#pragma unroll
-        for (int b = 0; b < MT; ++b) {
-          if constexpr (DEEP)
-            loc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s & 1][a], fb[s & 1][b], loc[a][b], 0, 0, 0);
-          else
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s & 1][a], fb[s & 1][b], acc[a][b], 0, 0, 0);
-        }
+      if constexpr (DEEP) loc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s & 1], fb[s & 1], loc, 0, 0, 0);
+      else acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s & 1], fb[s & 1], acc, 0, 0, 0);
     }
     if (DEEP && (++cnt == CHUNK || !more)) {
+      acc += loc;
 #pragma unroll
-      for (int a = 0; a < MT; ++a)
-#pragma unroll
-        for (int b = 0; b < MT; ++b) {
-          acc[a][b] += loc[a][b];
-#pragma unroll
-          for (int r = 0; r < 16; ++r) loc[a][b][r] = 0.0f;
-        }
+      for (int r = 0; r < 16; ++r) loc[r] = 0.0f;
       cnt = 0;
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -181,9 +151,8 @@ __device__ __forceinline__ void tile_product(const GemmF32& p, const float* A, c
   }
 }
 
-template <int BT, int TA, int TBT, bool VEC, bool DEEP>
+template <int TA, int TBT, bool VEC, bool DEEP>
 __global__ __launch_bounds__(256) void k_gemm_f32(GemmF32 p) {
-  constexpr int MT = BT / 64, BK = slice_k<BT>();
   if (ff_halted(p.st)) return;
   // With a triangular operand the k range, hence the work, of a tile grows
   // along one tile index: walk the tiles with that index slowest and from the
@@ -218,37 +187,29 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmF32 p) {
     B += (int64_t)blockIdx.z * p.sB;
     C += (int64_t)blockIdx.z * p.sC;
   }
-  __shared__ __align__(16) TileLDS<BT> sm;
+  __shared__ __align__(16) TileLDS sm;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 1, wn = wave & 1;
-  f32x16 acc[MT][MT];
+  f32x16 acc;
 #pragma unroll
-  for (int a = 0; a < MT; ++a)
-#pragma unroll
-    for (int b = 0; b < MT; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
   if (klo < khi) {
     const bool fast = VEC && i0 + BT <= p.M && j0 + BT <= p.N && (khi - klo) % BK == 0;
-    if (fast) tile_product<BT, TA == 0, TBT != 0, VEC, DEEP>(p, A, B, i0, j0, klo, khi, sm, acc);
-    else tile_product<BT, TA == 0, TBT != 0, false, DEEP>(p, A, B, i0, j0, klo, khi, sm, acc);
+    if (fast) tile_product<TA == 0, TBT != 0, VEC, DEEP>(p, A, B, i0, j0, klo, khi, sm, acc);
+    else tile_product<TA == 0, TBT != 0, false, DEEP>(p, A, B, i0, j0, klo, khi, sm, acc);
   }
   const bool lower = (p.flags & kCLower) != 0;
   const bool use_beta = p.ksplit <= 1 && p.beta != 0.0f;
 #pragma unroll
-  for (int a = 0; a < MT; ++a)
-#pragma unroll
-    for (int b = 0; b < MT; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t i = i0 + wm * (BT / 2) + a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int64_t j = j0 + wn * (BT / 2) + b * 32 + (lane & 31);
-        if (i < p.M && j < p.N && (!lower || i >= j)) {
-          float v = p.alpha * acc[a][b][r];
-          if (use_beta) v += p.beta * C[i * p.ldc + j];
-          C[i * p.ldc + j] = v;
-        }
-      }
+  for (int r = 0; r < 16; ++r) {
+    const int64_t i = i0 + wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    const int64_t j = j0 + wn * 32 + (lane & 31);
+    if (i < p.M && j < p.N && (!lower || i >= j)) {
+      float v = p.alpha * acc[r];
+      if (use_beta) v += p.beta * C[i * p.ldc + j];
+      C[i * p.ldc + j] = v;
+    }
+  }
 }
 
 __global__ __launch_bounds__(256) void k_reduce_rowmajor(const float* __restrict__ P, int splits,
@@ -270,19 +231,15 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 }  // namespace
 
-template <int BT>
-hipError_t launch_tiles(const GemmF32& p, int batch, bool vec, hipStream_t s) {
+hipError_t launch_tiles(const GemmF32& p, int batch, bool vec, bool deep, hipStream_t s) {
   const int64_t gx = (p.M + BT - 1) / BT, gy = (p.N + BT - 1) / BT;
   const int gz = p.ksplit > 1 ? p.ksplit : batch;
   if (gx > 0x7fffffff || gy > 65535 || gz > 65535) return hipErrorInvalidValue;
   const dim3 grid((uint32_t)gx, (uint32_t)gy, (uint32_t)gz);
-  // two-level accumulation when a workgroup's k range is long (the stacked samples)
-  const int64_t kwg = p.ksplit > 1 ? (p.K + p.ksplit - 1) / p.ksplit : p.K;
-  const bool deep = kwg > kDeepK;
   const int sel = (p.transA ? 1 : 0) | (p.transB ? 2 : 0) | (vec ? 4 : 0) | (deep ? 8 : 0);
   switch (sel) {
 #define FF_GEMM_CASE(c, ta, tb, v, dp) \
-    case c: hipLaunchKernelGGL((k_gemm_f32<BT, ta, tb, v, dp>), grid, dim3(256), 0, s, p); break;
+    case c: hipLaunchKernelGGL((k_gemm_f32<ta, tb, v, dp>), grid, dim3(256), 0, s, p); break;
     FF_GEMM_CASE(0, 0, 0, false, false)
     FF_GEMM_CASE(1, 1, 0, false, false)
     FF_GEMM_CASE(2, 0, 1, false, false)
@@ -298,7 +255,7 @@ hipError_t launch_tiles(const GemmF32& p, int batch, bool vec, hipStream_t s) {
     FF_GEMM_CASE(12, 0, 0, true, true)
     FF_GEMM_CASE(13, 1, 0, true, true)
     FF_GEMM_CASE(14, 0, 1, true, true)
-    default: hipLaunchKernelGGL((k_gemm_f32<BT, 1, 1, true, true>), grid, dim3(256), 0, s, p); break;
+    default: hipLaunchKernelGGL((k_gemm_f32<1, 1, true, true>), grid, dim3(256), 0, s, p); break;
 #undef FF_GEMM_CASE
   }
   return hipGetLastError();
@@ -309,17 +266,24 @@ hipError_t launch_gemm_f32(const GemmF32& p, int batch, hipStream_t s) {
   if (p.ksplit > 1 && batch != 1) return hipErrorInvalidValue;
   if (p.M == 0 || p.N == 0) return hipSuccess;
   const bool segmented = p.kseg < p.K;
+  // two-level accumulation when a workgroup's k range is long (the stacked samples)
+  const int64_t kwg = p.ksplit > 1 ? (p.K + p.ksplit - 1) / p.ksplit : p.K;
+  const bool deep = kwg > kDeepK;
   const bool vec = aligned16(p.A) && aligned16(p.B) && p.lda % 4 == 0 && p.ldb % 4 == 0 &&
                    (batch == 1 || (p.sA % 4 == 0 && p.sB % 4 == 0)) &&
                    (!segmented || (p.kseg % 4 == 0 && p.segA % 4 == 0 && p.segB % 4 == 0));
-  // 128 x 128 tiles when they fill the GPU, 64 x 64 (four times the workgroups) otherwise.
-  const int64_t big_tiles = ((p.M + 127) / 128) * ((p.N + 127) / 128) *
-                            (p.ksplit > 1 ? p.ksplit : batch);
   GemmF32 q = p;
   if (!segmented) q.kseg = 0;  // plain k axis: the kernels skip the segment arithmetic
-  if (p.tile == 64) return launch_tiles<64>(q, batch, vec, s);
-  if (p.tile == 128 || big_tiles >= 256) return launch_tiles<128>(q, batch, vec, s);
-  return launch_tiles<64>(q, batch, vec, s);
+  // From 256 tiles of 128 x 128 (128 of the split kernel's 256 x 128, half
+  // the CUs) the three-part products win: 4096 x 4096 x 4096 triangular 0.41 ms
+  // against 0.65 on the fp32 matrix cores (128 x 128 tiles); below, four times
+  // as many 64 x 64 tiles fill the GPU better.
+  const int64_t big_tiles = ((p.M + 127) / 128) * ((p.N + 127) / 128) *
+                            (p.ksplit > 1 ? p.ksplit : batch);
+  const bool square = !(p.flags & kCLower) || p.M == p.N;
+  if (p.tile != 64 && big_tiles >= 256 && square && p.lda <= kSplitMaxLd && p.ldb <= kSplitMaxLd)
+    return launch_gemm_split(q, batch, vec, deep, s);
+  return launch_tiles(q, batch, vec, deep, s);
 }
 
 hipError_t launch_reduce_rowmajor(const float* P, int splits, int64_t dim_p, float* F,

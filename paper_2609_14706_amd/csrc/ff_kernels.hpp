@@ -51,9 +51,11 @@ hipError_t launch_reduce_frag(const float* P, int splits, int64_t dim_p, float* 
 
 // ---------------------------------------------------------------- fp32 path
 enum GemmFlags : int {
-  kKHiRow = 1,   // k < i0 + 64   (left operand lower triangular)
+  // i0, j0: the tile's first row and column; the triangle's other side holds
+  // zeros up to the end of the tile at least
+  kKHiRow = 1,   // k < i0 + tile (left operand lower triangular)
   kKLoRow = 2,   // k >= i0       (left operand upper triangular)
-  kKHiCol = 4,   // k < j0 + 64   (right operand upper triangular)
+  kKHiCol = 4,   // k < j0 + tile (right operand upper triangular)
   kKLoCol = 8,   // k >= j0       (right operand lower triangular)
   kCLower = 16,  // write only C[i][j] with i >= j
 };
@@ -73,12 +75,18 @@ struct GemmF32 {
   int64_t segA, segB;
   int ksplit;          // > 1: grid z splits k, C += z * sC, beta ignored
   const int* st;
-  int tile;            // 0: chosen by size; 64: 64 x 64 tiles; 128: 128 x 128 tiles (a
-                       // workgroup reads all of its rows of op(A) before it writes, so C
-                       // may alias A when N <= 128)
+  int tile;            // 0: chosen by size; 64: 64 x 64 tiles
 };
-// C = alpha * op(A) op(B) + beta * C on the fp32 matrix cores (64 x 64 tiles).
+// C = alpha * op(A) op(B) + beta * C: on the fp32 matrix cores in 64 x 64
+// tiles, or, when it fills the GPU with larger ones, with launch_gemm_split.
 hipError_t launch_gemm_f32(const GemmF32& p, int batch, hipStream_t s);
+// The same on the bf16 matrix cores, every fp32 entry split into three bf16
+// parts; 256 x 128 tiles (ff_gemm_split.hip).  kseg = 0: plain k axis.  vec:
+// operands 16-byte aligned, leading dimensions, batch and segment strides
+// divisible by 4.  deep: k per workgroup beyond 16384.  With kCLower M = N;
+// lda, ldb <= kSplitMaxLd (32-bit offsets within a tile's slice).
+constexpr int64_t kSplitMaxLd = 1 << 23;
+hipError_t launch_gemm_split(const GemmF32& p, int batch, bool vec, bool deep, hipStream_t s);
 
 // F (dim x dim) = scale * sum_z P[z] with P[z] row-major dim_p x dim_p, lower
 // triangle read, mirrored.
