@@ -14,9 +14,8 @@
 //     (L11, X11) = cholinv(A11);  L21 = A21 X11^T;  A22 -= L21 L21^T;
 //     (L22, X22) = cholinv(A22);  X21 = -X22 (L21 X11)
 // with X = L^-1.  32 x 32 base blocks are factored and inverted by one wave
-// in registers (half the lanes hold rows of L, half columns of L^-1; each new
-// column of L is broadcast through LDS); the products run on the fp32 matrix
-// cores, one output tile per wave.  While wave 0 factors a base block, the
+// in the accumulators of rank-one matrix instructions; the products run on
+// the fp32 matrix cores, one output tile per wave.  While wave 0 factors a base block, the
 // other three waves do work off the pivot chain: the rest of the panel's
 // update of the block (first two base blocks) and the stores of the parts of
 // L and L^-1 already final (third).  A ragged block (b < 128) is padded with
@@ -37,12 +36,10 @@ constexpr int BS = 32;      // base block
 constexpr int SP = NB + 1;  // LDS row pitch (conflict-free column reads)
 
 struct LeafLDS {
-  float C[BS][BS];  // column j of the base block's L at pivot step j (first, so
-                    // its addresses fit the LDS instructions' immediate offset)
+  float C[BS][BS];  // product scratch of the 32-wide level
   float S[NB][SP];  // A, overwritten by L (lower triangle)
   float X[NB][SP];  // L^-1
   float T[64][65];  // product scratch
-  float dg[NB];  // diagonal of L (log-determinant)
   int bad;
 };
 
@@ -50,69 +47,73 @@ __device__ __forceinline__ float bcast(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-// Factor and invert the 32 x 32 block at (o, o) with one wave.  Lane r < 32
-// holds row r of the block, which becomes row r of L; lane 32 + r holds
-// column r of X = L^-1 (starting from the unit vector).  Pivot step j
-// scales entry j of every lane by 1 / L[j][j] (lane j keeps L[j][j]) and
-// subtracts v[j] times column j of L from entries j+1.. of every lane: for
-// the row lanes this is the Cholesky update, for the column lanes the
-// forward substitution of L X = I.  Only entry j+1 of that update lies on
-// the path to the next pivot: its multiplier L[j+1][j] is broadcast with
-// v_readlane and applied at the start of the next step.  The rest of the
-// column goes through LDS (sm.C[j][.], read back as uniform vectors) and is
-// applied one step later, off that path.  Row-lane entries above the
-// diagonal are never read for the lower triangle and are cleared at the end.
-// base_factor leaves the lane's row of L or column of X in v (and L[r][r]
-// in diag) and returns the block-relative failing column or -1;
-// base_store writes them to S and X and L[r][r] to dg.
-__device__ __forceinline__ int base_factor(LeafLDS& sm, int o, int lane, float (&v)[BS], float& diag) {
-  float col[BS], nxt[BS];
-  const int r = lane & 31;
-  const bool rowlane = lane < BS;
+typedef __attribute__((ext_vector_type(32))) float f32x32;
+
+// [v.lo, v.lo] (HI = false) or [v.hi, v.hi]: one half of the wave in both.
+template <bool HI>
+__device__ __forceinline__ float both_halves(float v) {
+  const uint32_t u = __float_as_uint(v);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(HI ? r[1] : r[0]);
+}
+
+// Factor and invert the 32 x 32 block at (o, o) with one wave, right-looking:
+// pivot step j takes row j of the trailing block (symmetric, so also its
+// column j) and of X = L^-1 (starting from I, the forward substitution of
+// L X = I), scales both by 1 / L[j][j] and subtracts the outer products
+//     L[., j] L[., j]^T   and   L[., j] X[j, .]
+// from the two 32 x 32 matrices, which live in the accumulators of one
+// two-block v_mfma_f32_32x32x1 (one product and one rounding per element, as
+// an fma): 64 cycles a step for all 2048 elements, off the pivot chain.  The
+// next pivot row itself is also updated by hand from the row the instruction
+// before left, so that the chain from pivot to pivot need not wait for it.
+// What bounds a step is the number of vector instructions of the one wave
+// (18, about 8 cycles each, and the exchanges of halves wait for the matrix
+// instruction): a block takes about 6.5k cycles.  With the rows in registers,
+// one fma per element and step, the column going round through LDS, it took
+// 11.4k, bitwise the same.  Rows and columns before j hold leftovers that
+// nothing reads.
+// base_factor leaves, in v[j] of lane r < 32, L[r][j], and of lane 32 + r,
+// X[j][r]; it returns the block-relative failing column or -1.  base_store
+// writes them to S (zeros above the diagonal) and X.
+__device__ __forceinline__ int base_factor(LeafLDS& sm, int o, int lane, float (&v)[BS]) {
+  const int col = lane & 31, hl = lane >> 5;
+  f32x32 d;
 #pragma unroll
-  for (int c = 0; c < BS; ++c) {
-    v[c] = rowlane ? (c <= r ? sm.S[o + r][o + c] : 0.0f) : (c == r ? 1.0f : 0.0f);
-    col[c] = 0.0f;
-    nxt[c] = 0.0f;
+  for (int r = 0; r < 16; ++r) {
+    const int row = 8 * (r >> 2) + 4 * hl + (r & 3);
+    d[r] = sm.S[o + (row > col ? row : col)][o + (row > col ? col : row)];
+    d[16 + r] = row == col ? 1.0f : 0.0f;
   }
   int bad = -1;
-  diag = 1.0f;                 // L[r][r] (row lanes)
-  float vp = 0.0f, lp = 0.0f;  // previous step's multiplier v[j-1] and L[j][j-1]
+  float rl = d[0], rx = d[16];  // row j of the trailing block and of X, valid in half (j / 4) % 2
 #pragma unroll
   for (int j = 0; j < BS; ++j) {
-    if (j > 0) v[j] -= vp * lp;  // last update of entry j (from step j-1)
-    const float d = bcast(v[j], j);
-    if (!(d > 0.0f) || !(d < INFINITY)) {
+    constexpr int kRegs[BS] = {0, 1, 2, 3, 0, 1, 2, 3, 4, 5, 6, 7, 4, 5, 6, 7,
+                               8, 9, 10, 11, 8, 9, 10, 11, 12, 13, 14, 15, 12, 13, 14, 15};
+    const bool hi = (j >> 2) & 1;
+    const float p = bcast(rl, (hi ? 32 : 0) + j);
+    if (!(p > 0.0f) || !(p < INFINITY)) {
       if (bad < 0) bad = j;
     }
-    const float rs = __builtin_amdgcn_rsqf(d), s = d * rs;  // 1 / L[j][j], L[j][j]
-    if (lane == j) diag = s;
-    const float vj = lane == j ? s : v[j] * rs;
-    v[j] = vj;
-    const float ln = j + 1 < BS ? bcast(vj, j + 1) : 0.0f;  // L[j+1][j]
-    if (j + 2 < BS) {
-      if (rowlane) sm.C[j][r] = vj;
-#pragma unroll
-      for (int c = j + 2; c < BS; ++c) nxt[c] = sm.C[j][c];  // L[c][j], uniform
+    const float rs = __builtin_amdgcn_rsqf(p);  // 1 / L[j][j]
+    rl *= rs;
+    rx *= rs;
+    const float lj = hi ? both_halves<true>(rl) : both_halves<false>(rl);  // L[., j]
+    const float xj = hi ? both_halves<true>(rx) : both_halves<false>(rx);  // X[j, .]
+    const float bv = lane < 32 ? lj : xj;
+    v[j] = bv;
+    if (j + 1 < BS) {
+      const float ln = bcast(lj, j + 1);  // L[j + 1][j]
+      rl = d[kRegs[j + 1]] - ln * lj;
+      rx = d[16 + kRegs[j + 1]] - ln * xj;
+      if (j + 2 < BS) d = __builtin_amdgcn_mfma_f32_32x32x1f32(-lj, bv, d, 0, 0, 0);
     }
-    // the rest of step j-1's update
-    if (j > 0) {
-#pragma unroll
-      for (int c = j + 1; c < BS; ++c) v[c] -= vp * col[c];
-    }
-    // bounded register lifetimes: step j-1 is complete here
-#pragma unroll
-    for (int c = j + 1; c < BS; ++c) asm volatile("" : "+v"(v[c]));
-#pragma unroll
-    for (int c = j + 2; c < BS; ++c) col[c] = nxt[c];
-    if (j + 1 < BS) col[j + 1] = 0.0f;  // entry j+1 is updated through lp instead
-    vp = vj;
-    lp = ln;
   }
   return bad;
 }
 
-__device__ __forceinline__ void base_store(LeafLDS& sm, int o, int lane, const float (&v)[BS], float diag) {
+__device__ __forceinline__ void base_store(LeafLDS& sm, int o, int lane, const float (&v)[BS]) {
   const int r = lane & 31;
   const bool rowlane = lane < BS;
   // one store per entry for all lanes: row r of S (row lanes) or column r
@@ -121,7 +122,6 @@ __device__ __forceinline__ void base_store(LeafLDS& sm, int o, int lane, const f
   const int step = rowlane ? 1 : SP;
 #pragma unroll
   for (int c = 0; c < BS; ++c) dst[c * step] = (rowlane && c > r) ? 0.0f : v[c];
-  if (rowlane) sm.dg[o + r] = diag;
 }
 
 // The products of a recursion level are h x h (h = 64 or 32) with k running
@@ -195,10 +195,10 @@ struct NoSide {
 template <class Side = NoSide>
 __device__ __forceinline__ void base_step(LeafLDS& sm, int o, int wave, int lane, int pre,
                                           const Side& side = Side()) {
-  float v[BS], diag = 1.0f;
+  float v[BS];
   int b = -1;
   if (wave == 0) {
-    b = base_factor(sm, o, lane, v, diag);
+    b = base_factor(sm, o, lane, v);
   } else if (pre == 1) {
     const int ts[2] = {wave, wave == 1 ? 4 : wave + 4};  // (1,0) (2,1) | (1,1) (3,0) | (2,0) (3,1)
     pre_update<2>(sm, lane, ts);
@@ -218,7 +218,7 @@ __device__ __forceinline__ void base_step(LeafLDS& sm, int o, int wave, int lane
     for (int e = 0; e < 4; ++e) sm.X[r][32 + c + e] = 0.0f;
   }
   if (wave == 0) {
-    base_store(sm, o, lane, v, diag);
+    base_store(sm, o, lane, v);
     if (lane == 0 && b >= 0 && sm.bad < 0) sm.bad = o + b;
   }
   __syncthreads();
@@ -584,10 +584,13 @@ __device__ __forceinline__ void leaf_body(LeafLDS& sm, const float* Lblk, float*
     return;
   }
   if (vec_out) {
-    // the rest: L22, L^-1 22 and L^-1 21
-    store64<256>(sm.X, 64, 64, Liblk + 64 * ld + 64, ld, 1, tid);
-    store64<256>(sm.X, 64, 0, Liblk + 64 * ld, ld, 0, tid);
-    if (Lout != nullptr) store64<256>(sm.S, 64, 64, Lout + 64 * ld + 64, ld, 1, tid);
+    // the rest: L22, L^-1 22 and L^-1 21, by waves 1..3 (wave 0 sums the
+    // log-determinant meanwhile)
+    if (wave > 0) {
+      store64<192>(sm.X, 64, 64, Liblk + 64 * ld + 64, ld, 1, tid - 64);
+      store64<192>(sm.X, 64, 0, Liblk + 64 * ld, ld, 0, tid - 64);
+      if (Lout != nullptr) store64<192>(sm.S, 64, 64, Lout + 64 * ld + 64, ld, 1, tid - 64);
+    }
   } else if (j < b) {
 #pragma unroll 8
     for (int i = i0; i < b; i += 2) Liblk[(int64_t)i * ld + j] = j <= i ? sm.X[i][j] : 0.0f;
@@ -599,7 +602,7 @@ __device__ __forceinline__ void leaf_body(LeafLDS& sm, const float* Lblk, float*
   // log-determinant share, sum of log L_jj over the block (kept off the
   // pivots' path; ragged blocks are padded with unit pivots)
   if (wave == 0) {
-    double ls = log((double)sm.dg[lane]) + log((double)sm.dg[lane + 64]);
+    double ls = log((double)sm.S[lane][lane]) + log((double)sm.S[lane + 64][lane + 64]);
 #pragma unroll
     for (int w = 32; w >= 1; w >>= 1) ls += __shfl_xor(ls, w, 64);
     if (lane == 0) logdet[slot] = ls;
