@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256) void k_scale_transpose_16(const bf16_t* __rest
 // sum_j F_jj (F^-1)_jj, since (F^-1)_jj is the squared norm of column j of
 // L^-1.
 template <typename T>
-__global__ __launch_bounds__(256) void k_convert_inverse(const float* __restrict__ Li, int64_t dim,
+__global__ __launch_bounds__(256) void k_convert_inverse(const float* __restrict__ Li, int64_t dim, int64_t ld,
                                                          T* __restrict__ Lw, T* __restrict__ Lw2,
                                                          int64_t dim_p, int64_t rch, int full,
                                                          const float* __restrict__ F,
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(256) void k_convert_inverse(const float* __restrict
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t r = i + u;
-        v[u] = (r < i1 && r < dim && j < dim && (full || j <= r)) ? Li[r * dim + j] : 0.0f;
+        v[u] = (r < i1 && r < dim && j < dim && (full || j <= r)) ? Li[r * ld + j] : 0.0f;
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -353,8 +353,9 @@ __global__ __launch_bounds__(256) void k_loglik(const double* slotsA, int nA, co
 }
 
 // Per-workgroup partial sums (fixed strided subsets, fixed-order reduction)
-// of sum Li^2 over dim x dim and of the diagonal of F.
-__global__ __launch_bounds__(256) void k_sumsq_trace(const float* __restrict__ Li,
+// of sum Li^2 over dim rows (leading dimension ld, zero beyond column dim)
+// and of the diagonal of F.
+__global__ __launch_bounds__(256) void k_sumsq_trace(const float* __restrict__ Li, int64_t ld,
                                                      const float* __restrict__ F, int64_t dim,
                                                      double* __restrict__ part, const int* st) {
   if (ff_halted(st)) return;
@@ -362,7 +363,7 @@ __global__ __launch_bounds__(256) void k_sumsq_trace(const float* __restrict__ L
   const int64_t stride = (int64_t)kDiagBlocks * 256;
   const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x;
   double ss = 0.0, tf = 0.0;
-  for (int64_t i = first; i < dim * dim; i += stride) {
+  for (int64_t i = first; i < dim * ld; i += stride) {
     const double v = (double)Li[i];
     ss += v * v;
   }
@@ -580,18 +581,18 @@ int64_t convert_parts(int64_t dim_p) {
   return ((dim_p + 255) / 256) * ((dim_p + rch - 1) / rch);
 }
 
-hipError_t launch_convert_inverse(const float* Li, int64_t dim, void* Lw, void* Lw2, int64_t dim_p,
-                                  int elem_bytes, const float* F, double* part, const int* st,
+hipError_t launch_convert_inverse(const float* Li, int64_t dim, int64_t ld, void* Lw, void* Lw2,
+                                  int64_t dim_p, int elem_bytes, const float* F, double* part, const int* st,
                                   hipStream_t s, int full) {
-  if (dim < 1 || dim_p < dim) return hipErrorInvalidValue;
+  if (dim < 1 || ld < dim || dim_p < dim) return hipErrorInvalidValue;
   const int64_t nchunk = dim_p < kConvertChunks ? dim_p : kConvertChunks;
   const int64_t rch = (dim_p + nchunk - 1) / nchunk;
   const dim3 grid((uint32_t)((dim_p + 255) / 256), (uint32_t)((dim_p + rch - 1) / rch));
   if (elem_bytes == 2)
-    hipLaunchKernelGGL(k_convert_inverse<bf16_t>, grid, dim3(256), 0, s, Li, dim, (bf16_t*)Lw,
+    hipLaunchKernelGGL(k_convert_inverse<bf16_t>, grid, dim3(256), 0, s, Li, dim, ld, (bf16_t*)Lw,
                        (bf16_t*)Lw2, dim_p, rch, full, F, part, st);
   else if (elem_bytes == 4)
-    hipLaunchKernelGGL(k_convert_inverse<float>, grid, dim3(256), 0, s, Li, dim, (float*)Lw,
+    hipLaunchKernelGGL(k_convert_inverse<float>, grid, dim3(256), 0, s, Li, dim, ld, (float*)Lw,
                        (float*)Lw2, dim_p, rch, full, F, part, st);
   else
     return hipErrorInvalidValue;
@@ -627,10 +628,10 @@ hipError_t launch_loglik(const double* slotsA, int nA, const double* slotsB, int
   return hipGetLastError();
 }
 
-hipError_t launch_sumsq_trace(const float* Li, const float* F, int64_t dim, double* part,
+hipError_t launch_sumsq_trace(const float* Li, int64_t ld, const float* F, int64_t dim, double* part,
                               const int* st, hipStream_t s) {
   if (dim < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_sumsq_trace, dim3(kDiagBlocks), dim3(256), 0, s, Li, F, dim, part, st);
+  hipLaunchKernelGGL(k_sumsq_trace, dim3(kDiagBlocks), dim3(256), 0, s, Li, ld, F, dim, part, st);
   return hipGetLastError();
 }
 

@@ -628,16 +628,16 @@ union StepLDS {
 // block column starts before jend (the diagonal block excluded), round robin
 // over block columns then rows.
 __global__ __launch_bounds__(256) void k_chol_step(float* __restrict__ L, float* __restrict__ Li,
-                                                   int64_t dim, int64_t d0, int64_t ok, int64_t jend,
+                                                   int64_t dim, int64_t ld, int64_t d0, int64_t ok, int64_t jend,
                                                    double* logdet, int iteration, int side, int* st) {
   if (ff_halted(st)) return;
   __shared__ StepLDS sm;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   if (blockIdx.x == 0) {
     const int b = (int)min<int64_t>(NB, dim - d0);
-    float* Akk = L + d0 * dim + d0;
-    leaf_body(sm.leaf, Akk, Li + d0 * dim + d0, dim, b, d0, logdet, (int)(d0 / NB), iteration, side,
-              st, Akk, ok >= 0 ? L + d0 * dim + ok : nullptr);
+    float* Akk = L + d0 * ld + d0;
+    leaf_body(sm.leaf, Akk, Li + d0 * ld + d0, ld, b, d0, logdet, (int)(d0 / NB), iteration, side,
+              st, Akk, ok >= 0 ? L + d0 * ld + ok : nullptr);
     return;
   }
   const int64_t R = (dim - d0 + NB - 1) / NB;   // block rows at or below d0
@@ -652,8 +652,8 @@ __global__ __launch_bounds__(256) void k_chol_step(float* __restrict__ L, float*
     }
     const int64_t bi = bj + u;
     const int64_t i0 = d0 + bi * NB, j0 = d0 + bj * NB;
-    load_rows(sm.trail.a, L, dim, i0, ok, dim, tid);
-    if (bi != bj) load_rows(sm.trail.b, L, dim, j0, ok, dim, tid);
+    load_rows(sm.trail.a, L, ld, i0, ok, dim, tid);
+    if (bi != bj) load_rows(sm.trail.b, L, ld, j0, ok, dim, tid);
     __syncthreads();
     // this lane's 64 entries of the block, read (from clamped addresses)
     // before the product so that their latency overlaps it
@@ -666,7 +666,7 @@ __global__ __launch_bounds__(256) void k_chol_step(float* __restrict__ L, float*
         for (int r = 0; r < 16; ++r) {
           const int64_t i = min<int64_t>(i0 + quad_row(wave, a, r, lane), dim - 1);
           const int64_t j = min<int64_t>(j0 + quad_col(wave, c, lane), dim - 1);
-          cv[a][c][r] = L[i * dim + j];
+          cv[a][c][r] = L[i * ld + j];
         }
     f32x16 u4[2][2];
     quad_product(sm.trail.a, bi != bj ? sm.trail.b : sm.trail.a, wave, lane, u4);
@@ -677,7 +677,7 @@ __global__ __launch_bounds__(256) void k_chol_step(float* __restrict__ L, float*
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int64_t i = i0 + quad_row(wave, a, r, lane), j = j0 + quad_col(wave, c, lane);
-          if (i < dim && j < dim && (bi != bj || j <= i)) L[i * dim + j] = cv[a][c][r] - u4[a][c][r];
+          if (i < dim && j < dim && (bi != bj || j <= i)) L[i * ld + j] = cv[a][c][r] - u4[a][c][r];
         }
     __syncthreads();  // before the next tile's rows overwrite LDS
   }
@@ -774,9 +774,9 @@ __global__ __launch_bounds__(256) void k_panel_solve(float* __restrict__ P, cons
 
 }  // namespace
 
-hipError_t launch_chol_step(float* L, float* Li, int64_t dim, int64_t d0, int64_t ok, int64_t jend,
-                            double* logdet, int iteration, int side, int* st, hipStream_t s) {
-  if (dim < 1 || d0 < 0 || d0 >= dim || d0 % kLeaf != 0) return hipErrorInvalidValue;
+hipError_t launch_chol_step(float* L, float* Li, int64_t dim, int64_t ld, int64_t d0, int64_t ok,
+                            int64_t jend, double* logdet, int iteration, int side, int* st, hipStream_t s) {
+  if (dim < 1 || ld < dim || d0 < 0 || d0 >= dim || d0 % kLeaf != 0) return hipErrorInvalidValue;
   if (ok >= 0 && (ok % kLeaf != 0 || ok + kLeaf > d0 || jend <= d0 || jend > dim))
     return hipErrorInvalidValue;
   int64_t ntiles = 0;
@@ -785,7 +785,7 @@ hipError_t launch_chol_step(float* L, float* Li, int64_t dim, int64_t d0, int64_
     ntiles = T * R - T * (T - 1) / 2 - 1;
   }
   const int64_t grid = 1 + std::min<int64_t>(ntiles, kStepWorkers);
-  hipLaunchKernelGGL(k_chol_step, dim3((uint32_t)grid), dim3(256), 0, s, L, Li, dim, d0,
+  hipLaunchKernelGGL(k_chol_step, dim3((uint32_t)grid), dim3(256), 0, s, L, Li, dim, ld, d0,
                      ok >= 0 ? ok : (int64_t)-1, jend, logdet, iteration, side, st);
   return hipGetLastError();
 }

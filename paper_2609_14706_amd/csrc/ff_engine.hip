@@ -54,6 +54,7 @@ int64_t round_up(int64_t x, int64_t g) { return (x + g - 1) / g * g; }
 
 struct Side {
   int64_t dim = 0, dim_p = 0;
+  int64_t ld = 0;                    // leading dimension of L and Li
   float* F[2] = {nullptr, nullptr};  // the factor, double buffered by iteration parity
   float* L = nullptr;                // Cholesky work copy
   float* Li = nullptr;               // L^-1 (fp32, lower)
@@ -79,6 +80,7 @@ struct Side {
 
 struct Layout {
   int64_t m_p, n_p;
+  int64_t ldA, ldB;  // leading dimensions of the factorisations (Side::ld)
   bool own_gx;
   bool rank1;
   int64_t T_p;  // rank-one form: padded token count
@@ -166,7 +168,14 @@ ff_status validate_shape(const ff_config* c) {
   return FF_OK;
 }
 
-Layout make_layout(const ff_config* c) {
+// Leading dimension of a factorisation's L and L^-1: with rows of whole
+// 16-byte vectors its kernels move float4s (a 2051-wide factor's panel takes
+// 9 us instead of 34, its step 30 instead of 47).
+int64_t factor_ld(int64_t dim) { return round_up(dim, 4); }
+
+// padded = false: factorisations at their own width, for a workspace that
+// has no room for factor_ld (what it holds is never refused for that).
+Layout make_layout(const ff_config* c, bool padded = true) {
   Layout L{};
   const int g = granule(c), e = elem_bytes(c);
   const int64_t m = c->m, n = c->n, N = c->N;
@@ -226,17 +235,19 @@ Layout make_layout(const ff_config* c) {
   L.off_split = split2 && c->whiten_split == 0
                     ? take(2 * (kAlign + align_up(sizeof(double) * convert_parts(dmax))))
                     : 0;
-  auto side = [&](size_t* o, int64_t dim, int64_t dim_p) {
-    const size_t fb = (size_t)dim * dim * sizeof(float);
+  L.ldA = padded ? factor_ld(n) : n;
+  L.ldB = padded ? factor_ld(m) : m;
+  auto side = [&](size_t* o, int64_t dim, int64_t dim_p, int64_t ld) {
+    const size_t fb = (size_t)dim * dim * sizeof(float), lb = (size_t)dim * ld * sizeof(float);
     o[0] = take(fb);
     o[1] = take(fb);
-    o[2] = take(fb);
-    o[3] = take(fb);
+    o[2] = take(lb);
+    o[3] = take(lb);
     o[4] = take((size_t)dim_p * dim_p * e);
     o[5] = split2 ? take((size_t)dim_p * dim_p * 2) : 0;
   };
-  side(L.off_A, n, L.n_p);
-  side(L.off_B, m, L.m_p);
+  side(L.off_A, n, L.n_p, L.ldA);
+  side(L.off_B, m, L.m_p, L.ldB);
   L.total = off;
   return L;
 }
@@ -342,7 +353,7 @@ struct TreeNode {
 };
 
 TreeNode tree_node(Side& s, int64_t o, int64_t sz) {
-  const int64_t d = s.dim;
+  const int64_t d = s.ld;
   const int64_t nl = (sz + kLeaf - 1) / kLeaf;
   TreeNode t;
   t.hh = (nl + 1) / 2 * kLeaf;
@@ -361,7 +372,7 @@ GemmF32 tree_gemm(ff_handle_s* h, Side& s, const TreeNode& t) {
   // one-level factor's few wide nodes run beside its steps (64 x 64 tiles: 4096
   // factor 2.03 ms either way)
   g.tile = s.dim <= kTwoLevel || t.hh < 2048 ? 64 : 0;
-  g.lda = g.ldb = g.ldc = s.dim;
+  g.lda = g.ldb = g.ldc = s.ld;
   g.kseg = INT64_MAX / 4;
   g.ksplit = 1;
   g.st = h->st;
@@ -448,7 +459,7 @@ ff_status chol_blocked(ff_handle_s* h, Side& s, int iteration) {
   const bool two = !h->single_stream;
   ff_status rc = two ? side_streams(s) : FF_OK;
   if (rc != FF_OK) return rc;
-  const int64_t d = s.dim;
+  const int64_t d = s.dim, ld = s.ld;
   const int64_t nb = (d + kLeaf - 1) / kLeaf;
   const int64_t outer = d > kTwoLevel ? kOuter : nb * kLeaf;
   hipStream_t ms = h->stream;
@@ -480,11 +491,11 @@ ff_status chol_blocked(ff_handle_s* h, Side& s, int iteration) {
   for (int64_t p = 0; p < d; p += outer) {
     const int64_t pe = std::min(p + outer, d);
     // the outer panel's first diagonal block has every earlier update
-    FF_HIP(launch_chol_step(s.L, s.Li, d, p, -1, 0, s.slots, iteration, s.code, h->st, ms));
+    FF_HIP(launch_chol_step(s.L, s.Li, d, ld, p, -1, 0, s.slots, iteration, s.code, h->st, ms));
     for (int64_t o = p; o + kLeaf < pe || (o + kLeaf < d && o + kLeaf == pe); o += kLeaf) {
       const int64_t k = o / kLeaf, rest = d - o - kLeaf;
       // the panel L_ik = A_ik Li_kk^T, in place
-      FF_HIP(launch_panel_solve(s.L + (o + kLeaf) * d + o, s.Li + o * d + o, d, rest, h->st, ms));
+      FF_HIP(launch_panel_solve(s.L + (o + kLeaf) * ld + o, s.Li + o * ld + o, ld, rest, h->st, ms));
       // every kInvEvery panels, and every second one among the last
       // kInvEvery and the one before the last leaf (the last steps leave most
       // CUs idle for the tree's products)
@@ -492,16 +503,16 @@ ff_status chol_blocked(ff_handle_s* h, Side& s, int iteration) {
       if (((k + 1) % kInvEvery == 0 || tail) && (rc = hand_over(k, true)) != FF_OK) return rc;
       if (o + kLeaf == pe) break;  // the last panel of the outer panel
       // diagonal block k + 1 and the panel's update of the outer panel's columns
-      FF_HIP(launch_chol_step(s.L, s.Li, d, o + kLeaf, o, pe, s.slots, iteration, s.code, h->st, ms));
+      FF_HIP(launch_chol_step(s.L, s.Li, d, ld, o + kLeaf, o, pe, s.slots, iteration, s.code, h->st, ms));
     }
     if (pe < d) {
       // A_22 -= L_21 L_21^T over the outer panel's columns
       GemmF32 g{};
-      g.lda = g.ldb = g.ldc = d;
+      g.lda = g.ldb = g.ldc = ld;
       g.kseg = INT64_MAX / 4;
       g.ksplit = 1;
       g.st = h->st;
-      g.A = s.L + pe * d + p; g.B = g.A; g.C = s.L + pe * d + pe;
+      g.A = s.L + pe * ld + p; g.B = g.A; g.C = s.L + pe * ld + pe;
       g.M = d - pe; g.N = d - pe; g.K = pe - p;
       g.transA = 0; g.transB = 1; g.alpha = -1.f; g.beta = 1.f; g.flags = kCLower;
       FF_HIP(launch_gemm_f32(g, 1, ms));
@@ -548,10 +559,13 @@ double samples_per_dim(const ff_handle_s* h) {
 // s.Lw; sum log L_jj per leaf into s.slots.
 ff_status cholinv_from(ff_handle_s* h, Side& s, const float* src, int iteration) {
   Timed t(h, 3, (double)s.dim * s.dim * s.dim / 3.0);
-  FF_HIP(launch_copy_f32(src, s.L, s.dim * s.dim, h->st, h->stream));
+  if (s.ld == s.dim)
+    FF_HIP(launch_copy_f32(src, s.L, s.dim * s.dim, h->st, h->stream));
+  else
+    FF_HIP(launch_copy2d_f32(src, s.dim, s.L, s.ld, s.dim, s.dim, h->st, h->stream));
   ff_status rc = chol_blocked(h, s, iteration);
   if (rc != FF_OK) return rc;
-  FF_HIP(launch_convert_inverse(s.Li, s.dim, s.Lw, s.Lw2, s.dim_p, h->elem, src, s.spart, h->st,
+  FF_HIP(launch_convert_inverse(s.Li, s.dim, s.ld, s.Lw, s.Lw2, s.dim_p, h->elem, src, s.spart, h->st,
                                 h->stream));
   if (s.split_flag != nullptr) {
     FF_HIP(launch_split_decide(s.spart, s.dim, s.dim_p, kSplitThreshold, s.split_flag,
@@ -574,7 +588,7 @@ ff_status cholinv(ff_handle_s* h, Side& s, int slot, int iteration) {
 // handled as the oracle handles it.
 ff_status frob_operand(ff_handle_s* h, Side& s, const float* src) {
   Timed t(h, 3, 0.0);
-  FF_HIP(launch_convert_inverse(src, s.dim, s.Lw, s.Lw2, s.dim_p, h->elem, nullptr, nullptr, h->st,
+  FF_HIP(launch_convert_inverse(src, s.dim, s.dim, s.Lw, s.Lw2, s.dim_p, h->elem, nullptr, nullptr, h->st,
                                 h->stream, 1));
   return FF_OK;
 }
@@ -922,7 +936,7 @@ ff_status iterate_chunk(ff_handle_s* h, int iters, int* done, double* loglik, do
     if (flipflop) {
       // with damping the trace term needs ||L^-1||_F^2 of the factor just factorised
       if (kappa > 0.0)
-        FF_HIP(launch_sumsq_trace(second.Li, second.F[slot], second.dim, h->spart, h->st,
+        FF_HIP(launch_sumsq_trace(second.Li, second.ld, second.F[slot], second.dim, h->spart, h->st,
                                   h->stream));
       FF_HIP(launch_loglik(h->A.slots, h->A.nslots, h->B.slots, h->B.nslots, h->c, bfirst ? 1 : 0,
                            (double)h->m, (double)h->n, (double)h->N, kappa,
@@ -1016,8 +1030,10 @@ ff_status init_handle(const ff_config* cfg, const Layout& lay, ff_handle_s* h) {
     h->S = ws + lay.off_s;
     h->wv = (float*)(ws + lay.off_wv);
   }
-  auto side = [&](Side& s, const size_t* o, int64_t dim, int64_t dim_p, int splits, int code) {
+  auto side = [&](Side& s, const size_t* o, int64_t dim, int64_t dim_p, int64_t ld, int splits,
+                  int code) {
     s.dim = dim;
+    s.ld = ld;
     s.dim_p = dim_p;
     s.F[0] = (float*)(ws + o[0]);
     s.F[1] = (float*)(ws + o[1]);
@@ -1035,8 +1051,8 @@ ff_status init_handle(const ff_config* cfg, const Layout& lay, ff_handle_s* h) {
     s.splits = splits;
     s.code = code;
   };
-  side(h->A, lay.off_A, h->n, lay.n_p, lay.splitsA, 1);
-  side(h->B, lay.off_B, h->m, lay.m_p, lay.splitsB, 2);
+  side(h->A, lay.off_A, h->n, lay.n_p, lay.ldA, lay.splitsA, 1);
+  side(h->B, lay.off_B, h->m, lay.m_p, lay.ldB, lay.splitsB, 2);
   h->A.start_identity = cfg->A0 == nullptr;
   h->B.start_identity = cfg->B0 == nullptr;
 
@@ -1057,9 +1073,10 @@ ff_status init_handle(const ff_config* cfg, const Layout& lay, ff_handle_s* h) {
       FF_HIP(launch_set_int(h->A.split_flag, 1, 0, h->stream));
       FF_HIP(launch_set_int(h->B.split_flag, 1, 0, h->stream));
     }
-    // Upper blocks of L^-1 are never written by the factorisation: zero once.
-    FF_HIP(launch_fill_f32(h->A.Li, n * n, 0.0f, h->stream));
-    FF_HIP(launch_fill_f32(h->B.Li, m * m, 0.0f, h->stream));
+    // Upper blocks of L^-1 and the columns beyond it are never written by the
+    // factorisation: zero once.
+    FF_HIP(launch_fill_f32(h->A.Li, n * lay.ldA, 0.0f, h->stream));
+    FF_HIP(launch_fill_f32(h->B.Li, m * lay.ldB, 0.0f, h->stream));
     if (cfg->A0 != nullptr)
       FF_HIP(hipMemcpyAsync(h->A.F[0], cfg->A0, n * n * sizeof(float), hipMemcpyDeviceToDevice,
                             h->stream));
@@ -1118,13 +1135,13 @@ QuantLayout quant_layout(int64_t m, int64_t n) {
 // scales of one side: J M J is factorised in s.L / s.Li.
 ff_status quant_side(ff_handle_s* h, Side& s, const float* M, int64_t dq, float* Lt, float* diag,
                      double gamma, int given, float* user, float* scale) {
-  FF_HIP(launch_wk_reverse(M, s.dim, s.L, h->st, h->stream));
+  FF_HIP(launch_wk_reverse(M, s.dim, s.L, s.ld, h->st, h->stream));
   {
     Timed t(h, 3, (double)s.dim * s.dim * s.dim / 3.0);
     ff_status rc = chol_blocked(h, s, -1);
     if (rc != FF_OK) return rc;
   }
-  FF_HIP(launch_wk_normalise(s.Li, s.dim, dq, Lt, diag, h->st, h->stream));
+  FF_HIP(launch_wk_normalise(s.Li, s.ld, s.dim, dq, Lt, diag, h->st, h->stream));
   FF_HIP(launch_wk_scales(diag, s.dim, dq, s.slots, s.nslots, gamma, given, user, scale, h->st,
                           h->stream));
   return FF_OK;
@@ -1207,7 +1224,8 @@ ff_status ff_init(const ff_config* cfg, ff_handle* out) {
   ff_status rc = validate_config(cfg);
   if (rc != FF_OK) return rc;
   if (out == nullptr) return fail(FF_ERR_INVALID_ARG, "out is NULL");
-  const Layout lay = make_layout(cfg);
+  Layout lay = make_layout(cfg);
+  if (cfg->workspace_bytes < lay.total) lay = make_layout(cfg, false);
   if (cfg->workspace == nullptr || ((uintptr_t)cfg->workspace % kAlign) != 0)
     return fail(FF_ERR_WORKSPACE, "workspace must be a non-NULL 256-byte aligned device pointer");
   if (cfg->workspace_bytes < lay.total) {
@@ -1239,7 +1257,8 @@ ff_status ff_fit_noalloc(const ff_config* cfg, int iters, int* iters_done, doubl
   if (iters < 0) return fail(FF_ERR_INVALID_ARG, "iters must be >= 0");
   if (A == nullptr || B == nullptr || ((uintptr_t)A % 16) != 0 || ((uintptr_t)B % 16) != 0)
     return fail(FF_ERR_INVALID_ARG, "A and B must be non-NULL 16-byte aligned device pointers");
-  const Layout lay = make_layout(cfg);
+  Layout lay = make_layout(cfg);
+  if (lay.total > (size_t)FF_NOALLOC_SCRATCH_BYTES) lay = make_layout(cfg, false);
   if (lay.total > (size_t)FF_NOALLOC_SCRATCH_BYTES) {
     char msg[192];
     snprintf(msg, sizeof msg,
@@ -1365,10 +1384,10 @@ ff_status ff_kron_apply(ff_handle h, const float* X, float* Y, int64_t batch, ff
       if ((rc = gemm(T, n, mn, 0, h->A.F[cur], n, 0, 0, Yc, m, n, n, 0)) != FF_OK) return rc;
     } else {
       // B^-1 X A^-1 = Li_B^T Li_B X Li_A^T Li_A
-      if ((rc = gemm(h->B.Li, m, 0, 0, Xc, n, mn, 0, T, m, n, m, kKHiRow)) != FF_OK) return rc;
-      if ((rc = gemm(h->B.Li, m, 0, 1, T, n, mn, 0, Yc, m, n, m, kKLoRow)) != FF_OK) return rc;
-      if ((rc = gemm(Yc, n, mn, 0, h->A.Li, n, 0, 1, T, m, n, n, kKHiCol)) != FF_OK) return rc;
-      if ((rc = gemm(T, n, mn, 0, h->A.Li, n, 0, 0, Yc, m, n, n, kKLoCol)) != FF_OK) return rc;
+      if ((rc = gemm(h->B.Li, h->B.ld, 0, 0, Xc, n, mn, 0, T, m, n, m, kKHiRow)) != FF_OK) return rc;
+      if ((rc = gemm(h->B.Li, h->B.ld, 0, 1, T, n, mn, 0, Yc, m, n, m, kKLoRow)) != FF_OK) return rc;
+      if ((rc = gemm(Yc, n, mn, 0, h->A.Li, h->A.ld, 0, 1, T, m, n, n, kKHiCol)) != FF_OK) return rc;
+      if ((rc = gemm(T, n, mn, 0, h->A.Li, h->A.ld, 0, 0, Yc, m, n, n, kKLoCol)) != FF_OK) return rc;
     }
   }
   int st[4];
@@ -1421,20 +1440,21 @@ ff_status ff_objective(ff_handle h, const float* A, const float* B, double* psi)
   // M = (1/(N n)) sum_i G_i A^-1 G_i^T into the spare B buffer (no damping)
   if ((rc = update(h, h->B, h->A, spare, false)) != FF_OK) return rc;
   // Y = L_B^-1 M; tr(B^-1 M) = sum_jk Y_jk (L_B^-1)_jk
-  const int64_t m = h->m;
+  const int64_t m = h->m, ld = h->B.ld;
+  if (ld != m) FF_HIP(launch_fill_f32(h->B.L, m * ld, 0.0f, h->stream));  // the columns beyond Y
   GemmF32 g{};
   g.st = h->st;
   g.kseg = INT64_MAX / 4;
   g.ksplit = 1;
-  g.A = h->B.Li; g.lda = m; g.transA = 0;
+  g.A = h->B.Li; g.lda = ld; g.transA = 0;
   g.B = h->B.F[spare]; g.ldb = m; g.transB = 0;
-  g.C = h->B.L; g.ldc = m;
+  g.C = h->B.L; g.ldc = ld;
   g.M = m; g.N = m; g.K = m;
   g.alpha = 1.f; g.beta = 0.f; g.flags = kKHiRow;
   FF_HIP(launch_gemm_f32(g, 1, h->stream));
   double* scratch = reinterpret_cast<double*>(h->P);
   double* out = scratch + 512;
-  FF_HIP(launch_objective_terms(h->B.L, h->B.Li, m * m, h->A.slots, h->A.nslots, h->B.slots,
+  FF_HIP(launch_objective_terms(h->B.L, h->B.Li, m * ld, h->A.slots, h->A.nslots, h->B.slots,
                                 h->B.nslots, scratch, out, h->st, h->stream));
   double terms[3];
   FF_HIP(hipMemcpyAsync(terms, out, sizeof terms, hipMemcpyDeviceToHost, h->stream));

@@ -97,7 +97,8 @@ hipError_t launch_reduce_rowmajor(const float* P, int splits, int64_t dim_p, flo
 constexpr int kLeaf = 128;  // diagonal block factorised inside one workgroup
 
 // One step of the right-looking blocked factorisation of the dim x dim
-// matrix L (row-major, lower triangle; L^-1 blocks into Li): the diagonal
+// matrix L (row-major, leading dimension ld, lower triangle; L^-1 blocks into
+// Li, laid out alike): the diagonal
 // block at d0 (a multiple of 128) is factored and inverted in one workgroup
 // (pivots d0.., log-determinant share into logdet[d0 / 128], factor written
 // in place, L^-1 block into Li; a non-positive or NaN pivot sets the status
@@ -112,8 +113,8 @@ constexpr int kStepWorkers = 255;
 // block (lower, zeros above; leading dimension ld).
 hipError_t launch_panel_solve(float* P, const float* Xkk, int64_t ld, int64_t rows, const int* st,
                               hipStream_t s);
-hipError_t launch_chol_step(float* L, float* Li, int64_t dim, int64_t d0, int64_t ok, int64_t jend,
-                            double* logdet, int iteration, int side, int* st, hipStream_t s);
+hipError_t launch_chol_step(float* L, float* Li, int64_t dim, int64_t ld, int64_t d0, int64_t ok,
+                            int64_t jend, double* logdet, int iteration, int side, int* st, hipStream_t s);
 
 // out[s][r][c] (rows_p x cols_p) from G[s] (m x n): copy (transpose = 0,
 // rows_p >= m, cols_p >= n) or transpose (transpose = 1, rows_p >= n,
@@ -121,7 +122,8 @@ hipError_t launch_chol_step(float* L, float* Li, int64_t dim, int64_t d0, int64_
 hipError_t launch_pack(const void* G, void* out, int64_t N, int64_t m, int64_t n, int64_t rows_p,
                        int64_t cols_p, int transpose, int elem_bytes, hipStream_t s);
 
-// Lw (dim_p x dim_p, elem) = lower(Li) (all of Li with full = 1) rounded
+// Lw (dim_p x dim_p, elem) = lower(Li) (all of Li with full = 1; leading
+// dimension ld) rounded
 // (bf16: hi part; Lw2: lo part if non-null), zero elsewhere.  elem_bytes = 2
 // or 4.  With part non-null (and full = 0),
 // convert_parts(dim_p) partial sums of sum_j F_jj ||column j of lower(Li)||^2
@@ -129,8 +131,8 @@ hipError_t launch_pack(const void* G, void* out, int64_t N, int64_t m, int64_t n
 // of launch_split_decide).
 constexpr int64_t kConvertChunks = 64;
 int64_t convert_parts(int64_t dim_p);
-hipError_t launch_convert_inverse(const float* Li, int64_t dim, void* Lw, void* Lw2, int64_t dim_p,
-                                  int elem_bytes, const float* F, double* part, const int* st,
+hipError_t launch_convert_inverse(const float* Li, int64_t dim, int64_t ld, void* Lw, void* Lw2,
+                                  int64_t dim_p, int elem_bytes, const float* F, double* part, const int* st,
                                   hipStream_t s, int full = 0);
 
 // From those partials: out[0] = s = (1/dim) sum_j F_jj (F^-1)_jj and
@@ -158,9 +160,9 @@ hipError_t launch_loglik(const double* slotsA, int nA, const double* slotsB, int
                          double kappa, const double* part, double* ll_out, const int* st,
                          hipStream_t s);
 
-// part[2 b] / part[2 b + 1]: fixed-order partial sums of Li^2 (dim x dim)
-// and of diag(F), b < kDiagBlocks.
-hipError_t launch_sumsq_trace(const float* Li, const float* F, int64_t dim, double* part,
+// part[2 b] / part[2 b + 1]: fixed-order partial sums of Li^2 (dim rows of
+// leading dimension ld, zero beyond column dim) and of diag(F), b < kDiagBlocks.
+hipError_t launch_sumsq_trace(const float* Li, int64_t ld, const float* F, int64_t dim, double* part,
                               const int* st, hipStream_t s);
 
 // *delta_out = ||A (x) B - Ap (x) Bp||_F / (||Ap||_F ||Bp||_F) in fp64 (part:
@@ -231,11 +233,12 @@ struct WkParams {
   const int* st;
 };
 
-// J M J for M d x d.
-hipError_t launch_wk_reverse(const float* M, int64_t d, float* out, const int* st, hipStream_t s);
+// J M J for M d x d (out: leading dimension ldo).
+hipError_t launch_wk_reverse(const float* M, int64_t d, float* out, int64_t ldo, const int* st,
+                             hipStream_t s);
 // Normalised inverse of RevCholesky(M) (padded dq x dq) and its diagonal,
-// from Ci = Cholesky(J M J)^-1.
-hipError_t launch_wk_normalise(const float* Ci, int64_t d, int64_t dq, float* Lt, float* diag,
+// from Ci = Cholesky(J M J)^-1 (leading dimension ld).
+hipError_t launch_wk_normalise(const float* Ci, int64_t ld, int64_t d, int64_t dq, float* Lt, float* diag,
                                const int* st, hipStream_t s);
 // Padded scales; given = 0: waterfilling from diag and the log-pivot slots
 // (also written to user), given = 1: copied from user.

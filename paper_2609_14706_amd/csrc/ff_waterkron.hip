@@ -49,21 +49,21 @@ constexpr int OP = 96;   // operand pitch: rows k and k + 1 fall in opposite ban
 // ------------------------------------------------------------ preparation
 // out[i][j] = M[d-1-i][d-1-j]  (J M J)
 __global__ __launch_bounds__(256) void k_wk_reverse(const float* __restrict__ M, int64_t d,
-                                                    float* __restrict__ out, const int* st) {
+                                                    float* __restrict__ out, int64_t ldo, const int* st) {
   if (ff_halted(st)) return;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= d * d) return;
   const int64_t i = idx / d, j = idx % d;
-  out[idx] = M[(d - 1 - i) * d + (d - 1 - j)];
+  out[i * ldo + j] = M[(d - 1 - i) * d + (d - 1 - j)];
 }
 
-// Ci = C^-1 with C = Cholesky(J M J) (d x d, ld d).  RevCholesky(M) = J C^T J,
+// Ci = C^-1 with C = Cholesky(J M J) (d x d, leading dimension ld).  RevCholesky(M) = J C^T J,
 // its inverse is J C^-T J, whose entry (i, j) is Ci[d-1-j][d-1-i]; dividing
 // column j by its diagonal entry gives the normalised inverse
 //   Lt[i][j] = Ci[d-1-j][d-1-i] / Ci[d-1-j][d-1-j]   (i >= j),
 // written padded to dq x dq with the identity outside d x d.  diag[j] =
 // RevCholesky(M)_jj = 1 / Ci[d-1-j][d-1-j] (0 in the padding).
-__global__ __launch_bounds__(256) void k_wk_normalise(const float* __restrict__ Ci, int64_t d,
+__global__ __launch_bounds__(256) void k_wk_normalise(const float* __restrict__ Ci, int64_t ld, int64_t d,
                                                       int64_t dq, float* __restrict__ Lt,
                                                       float* __restrict__ diag, const int* st) {
   if (ff_halted(st)) return;
@@ -73,8 +73,8 @@ __global__ __launch_bounds__(256) void k_wk_normalise(const float* __restrict__ 
   float v;
   if (i < d && j < d) {
     const int64_t r = d - 1 - j;
-    const float dj = Ci[r * d + r];
-    v = i >= j ? Ci[r * d + (d - 1 - i)] / dj : 0.0f;
+    const float dj = Ci[r * ld + r];
+    v = i >= j ? Ci[r * ld + (d - 1 - i)] / dj : 0.0f;
     if (i == j) diag[j] = 1.0f / dj;
   } else {
     v = i == j ? 1.0f : 0.0f;
@@ -545,16 +545,17 @@ int64_t wk_push_units(int d, int MT, int NT) {
   return units;
 }
 
-hipError_t launch_wk_reverse(const float* M, int64_t d, float* out, const int* st, hipStream_t s) {
+hipError_t launch_wk_reverse(const float* M, int64_t d, float* out, int64_t ldo, const int* st,
+                             hipStream_t s) {
   if (d < 1 || d > (1 << 20)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_wk_reverse, dim3(blocks_for(d * d)), dim3(256), 0, s, M, d, out, st);
+  hipLaunchKernelGGL(k_wk_reverse, dim3(blocks_for(d * d)), dim3(256), 0, s, M, d, out, ldo, st);
   return hipGetLastError();
 }
 
-hipError_t launch_wk_normalise(const float* Ci, int64_t d, int64_t dq, float* Lt, float* diag,
+hipError_t launch_wk_normalise(const float* Ci, int64_t ld, int64_t d, int64_t dq, float* Lt, float* diag,
                                const int* st, hipStream_t s) {
   if (d < 1 || dq < d || dq % WT != 0 || dq > (1 << 20)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_wk_normalise, dim3(blocks_for(dq * dq)), dim3(256), 0, s, Ci, d, dq, Lt,
+  hipLaunchKernelGGL(k_wk_normalise, dim3(blocks_for(dq * dq)), dim3(256), 0, s, Ci, ld, d, dq, Lt,
                      diag, st);
   return hipGetLastError();
 }
