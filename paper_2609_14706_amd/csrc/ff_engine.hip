@@ -81,7 +81,8 @@ struct Side {
 struct Layout {
   int64_t m_p, n_p;
   int64_t ldA, ldB;  // leading dimensions of the factorisations (Side::ld)
-  bool own_gx;
+  bool own_gx;   // a padded copy of G (rank-one form: of x); otherwise the caller's
+  bool own_g;    // rank-one form: a padded copy of g
   bool rank1;
   int64_t T_p;  // rank-one form: padded token count
   // dense: gx = padded G, gt = padded transposed G, w = whitened samples;
@@ -182,8 +183,11 @@ Layout make_layout(const ff_config* c, bool padded = true) {
   L.m_p = round_up(m, g);
   L.n_p = round_up(n, g);
   L.rank1 = c->form == FF_SAMPLES_RANK1;
-  L.own_gx = L.rank1 || !(L.m_p == m && L.n_p == n);
   L.T_p = L.rank1 ? round_up(N, 256) : 0;  // a multiple of the token segment (and of g)
+  // tokens and samples that need no padding are read where the caller has
+  // them (524288 tokens of 4096: 7 ms of copies)
+  L.own_gx = L.rank1 ? !(L.T_p == N && L.n_p == n) : !(L.m_p == m && L.n_p == n);
+  L.own_g = L.rank1 && !(L.T_p == N && L.m_p == m);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;
@@ -199,8 +203,8 @@ Layout make_layout(const ff_config* c, bool padded = true) {
   L.off_slotsB = take(sizeof(double) * ((m + kLeaf - 1) / kLeaf));
   const int64_t dmax = std::max(L.m_p, L.n_p);
   if (L.rank1) {
-    L.off_gx = take((size_t)L.T_p * L.n_p * e);
-    L.off_gt = take((size_t)L.T_p * L.m_p * e);
+    L.off_gx = L.own_gx ? take((size_t)L.T_p * L.n_p * e) : 0;
+    L.off_gt = L.own_g ? take((size_t)L.T_p * L.m_p * e) : 0;
     L.w_bytes = std::max(is_bf16(c) ? (size_t)L.T_p * 2 * (dmax / kTileBF16) * sizeof(float)
                                     : (size_t)L.T_p * dmax * sizeof(float),
                          (size_t)m * n * sizeof(float));
@@ -264,8 +268,8 @@ struct ff_handle_s {
   bool bf16 = false;
   int elem = 4;
   Layout lay{};
-  const void* Gx = nullptr;
-  void* Gt = nullptr;
+  const void* Gx = nullptr;  // samples, or tokens x
+  const void* Gt = nullptr;  // transposed samples, or tokens g
   void* W = nullptr;
   float* P = nullptr;
   void* S = nullptr;      // rank-one form: weighted transposed tokens
@@ -624,10 +628,17 @@ const bf16_t* second_part(const ff_handle_s* h, const Side& p, const int** use2,
 // Rank-one form: token weights wbuf[t] = ||L_p^-1 v_t||^2 for the token
 // vectors v_t of side p's dimension (x_t when p = A, g_t when p = B); for
 // the Frobenius estimator v_t^T F_p v_t, from P = V F_p and a row-wise dot
-// product with V.
-ff_status token_weights(ff_handle_s* h, Side& p, float* wbuf) {
+// product with V.  identity: p's factor is exactly I (the default start), so
+// every estimator's weight is the token's squared norm, one pass over the
+// tokens instead of a product with I (and its factorisation): 8.4 + 2 ms of
+// 524288 tokens of 4096 become 0.9.
+ff_status token_weights(ff_handle_s* h, Side& p, float* wbuf, bool identity = false) {
   const void* V = (&p == &h->A) ? h->Gx : h->Gt;
   const int64_t T_p = h->lay.T_p, Kp = p.dim_p;
+  if (identity) {
+    FF_HIP(launch_row_dot(V, V, T_p, Kp, h->elem, wbuf, h->st, h->stream));
+    return FF_OK;
+  }
   const bool frob = h->cfg.estimator == FF_EST_FROBENIUS;
   const double wflop = (frob ? 2.0 : 1.0) * (double)h->N * p.dim * p.dim;
   Timed t(h, 0, wflop);
@@ -682,14 +693,14 @@ ff_status token_weights(ff_handle_s* h, Side& p, float* wbuf) {
 // unit: all weights 1 and scale 1/N (the token mean E[u u^T] of the Marginal
 // and Input estimators, Table 1).
 ff_status update_rank1(ff_handle_s* h, Side& s, Side& p, int slot, bool finish,
-                       bool unit = false, float* dst = nullptr) {
+                       bool unit = false, float* dst = nullptr, bool p_identity = false) {
   float* F = dst != nullptr ? dst : s.F[slot];
   float* wbuf = h->wv;
   const int64_t T_p = h->lay.T_p;
   if (unit) {
     FF_HIP(launch_fill_f32(wbuf, T_p, 1.0f, h->stream));
   } else {
-    ff_status rc = token_weights(h, p, wbuf);
+    ff_status rc = token_weights(h, p, wbuf, p_identity);
     if (rc != FF_OK) return rc;
   }
   const void* U = (&s == &h->B) ? h->Gt : h->Gx;
@@ -738,7 +749,7 @@ ff_status update_rank1(ff_handle_s* h, Side& s, Side& p, int slot, bool finish,
 // (twice the whitening's work), then the upper tiles of P X^T.
 ff_status update(ff_handle_s* h, Side& s, Side& p, int slot, bool finish = true,
                  bool p_identity = false, float* dst = nullptr) {
-  if (h->lay.rank1) return update_rank1(h, s, p, slot, finish, false, dst);
+  if (h->lay.rank1) return update_rank1(h, s, p, slot, finish, false, dst, p_identity);
   float* F = dst != nullptr ? dst : s.F[slot];
   const void* X = (&s == &h->B) ? h->Gx : h->Gt;
   const int64_t N = h->N, rows = N * s.dim_p, Kp = p.dim_p;
@@ -919,7 +930,7 @@ ff_status iterate_chunk(ff_handle_s* h, int iters, int* done, double* loglik, do
   ff_status rc;
   // Before the first iteration the factor updated second may still be the
   // default start I: its whitening operand is I, nothing to factorise or apply.
-  const bool start_id = base == 0 && second.start_identity && !h->lay.rank1;
+  const bool start_id = base == 0 && second.start_identity;
   if (!second.lw_valid && !start_id) {
     rc = operand(h, second, h->cur, (int)(base + 1));
     if (rc != FF_OK) return rc;
@@ -1022,8 +1033,8 @@ ff_status init_handle(const ff_config* cfg, const Layout& lay, ff_handle_s* h) {
   h->B.slots = (double*)(ws + lay.off_slotsB);
   h->A.nslots = (int)((h->n + kLeaf - 1) / kLeaf);
   h->B.nslots = (int)((h->m + kLeaf - 1) / kLeaf);
-  h->Gx = lay.own_gx ? (const void*)(ws + lay.off_gx) : cfg->G;
-  h->Gt = ws + lay.off_gt;
+  h->Gx = lay.own_gx ? (const void*)(ws + lay.off_gx) : lay.rank1 ? cfg->x : cfg->G;
+  h->Gt = lay.rank1 && !lay.own_g ? cfg->g : (const void*)(ws + lay.off_gt);
   h->W = ws + lay.off_w;
   h->P = (float*)(ws + lay.off_p);
   if (lay.rank1) {
@@ -1061,12 +1072,14 @@ ff_status init_handle(const ff_config* cfg, const Layout& lay, ff_handle_s* h) {
     const int64_t N = h->N, m = h->m, n = h->n;
     if (lay.rank1) {
       // tokens as one padded matrix each: x -> T_p x n_p, g -> T_p x m_p
-      FF_HIP(launch_pack(cfg->x, (void*)h->Gx, 1, N, n, lay.T_p, lay.n_p, 0, h->elem, h->stream));
-      FF_HIP(launch_pack(cfg->g, h->Gt, 1, N, m, lay.T_p, lay.m_p, 0, h->elem, h->stream));
+      if (lay.own_gx)
+        FF_HIP(launch_pack(cfg->x, (void*)h->Gx, 1, N, n, lay.T_p, lay.n_p, 0, h->elem, h->stream));
+      if (lay.own_g)
+        FF_HIP(launch_pack(cfg->g, (void*)h->Gt, 1, N, m, lay.T_p, lay.m_p, 0, h->elem, h->stream));
     } else {
       if (lay.own_gx)
         FF_HIP(launch_pack(cfg->G, (void*)h->Gx, N, m, n, lay.m_p, lay.n_p, 0, h->elem, h->stream));
-      FF_HIP(launch_pack(cfg->G, h->Gt, N, m, n, lay.n_p, lay.m_p, 1, h->elem, h->stream));
+      FF_HIP(launch_pack(cfg->G, (void*)h->Gt, N, m, n, lay.n_p, lay.m_p, 1, h->elem, h->stream));
     }
     // automatic split: no factor is known to need the second pass yet
     if (h->A.split_flag != nullptr) {

@@ -172,7 +172,8 @@ hipError_t launch_delta(const float* A, const float* Ap, int64_t nA, const float
                         const float* Bp, int64_t nB, double* part, double* delta_out, double tol,
                         int iteration, int* st, hipStream_t s);
 
-// w[r] = sum_j P[r][j] V[r][j], rows x cols, elem_bytes 2 (bf16) or 4.
+// w[r] = sum_j P[r][j] V[r][j], rows x cols (cols a multiple of 64, P and V
+// 16-byte aligned), elem_bytes 2 (bf16) or 4; P = V: the rows' squared norms.
 hipError_t launch_row_dot(const void* P, const void* V, int64_t rows, int64_t cols, int elem_bytes,
                           float* w, const int* st, hipStream_t s);
 
