@@ -443,15 +443,16 @@ __device__ __forceinline__ void store64(const float (*src)[SP], int r0, int c0, 
 // sets st = {iteration, side, pivot_base + j} and returns (the outputs then
 // hold partial results, at most the first half's).  Lpre (optional): the
 // block row of the last panel to the left (b rows x 128, leading dimension
-// ld), whose update A -= Lpre Lpre^T is applied to the block first.
+// ld), whose update A -= Lpre Lpre^T is applied to the block first.  lds: the
+// leading dimension of Lblk (L and L^-1 have ld).
 __device__ __forceinline__ void leaf_body(LeafLDS& sm, const float* Lblk, float* __restrict__ Liblk,
                                           int64_t ld, int b, int64_t pivot_base, double* logdet,
                                           int slot, int iteration, int side, int* st, float* Lout,
-                                          const float* Lpre) {
+                                          const float* Lpre, int64_t lds) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int j = tid & (NB - 1), i0 = tid >> 7;
   bool pre_loaded = false;  // Lpre already staged in X
-  if (b == NB && (ld & 3) == 0 && (reinterpret_cast<uintptr_t>(Lblk) & 15) == 0) {
+  if (b == NB && (ld & 3) == 0 && (lds & 3) == 0 && (reinterpret_cast<uintptr_t>(Lblk) & 15) == 0) {
     // full block, float4 moves (quad4_map); all sixteen loads (thirty-two
     // with the panel's block row) are in flight before the first is used
     int r, c;
@@ -460,7 +461,7 @@ __device__ __forceinline__ void leaf_body(LeafLDS& sm, const float* Lblk, float*
     float4 v[NB / 8], u[NB / 8];
 #pragma unroll
     for (int t = 0; t < NB / 8; ++t)
-      v[t] = *reinterpret_cast<const float4*>(Lblk + (int64_t)(r + 8 * t) * ld + c);
+      v[t] = *reinterpret_cast<const float4*>(Lblk + (int64_t)(r + 8 * t) * lds + c);
     if (pre) {
 #pragma unroll
       for (int t = 0; t < NB / 8; ++t)
@@ -493,7 +494,7 @@ __device__ __forceinline__ void leaf_body(LeafLDS& sm, const float* Lblk, float*
 #pragma unroll
       for (int t = 0; t < NB / 4; ++t) {
         const int i = i0 + 2 * (half * (NB / 4) + t);
-        const float x = Lblk[(int64_t)min(i, b - 1) * ld + min(j, b - 1)];
+        const float x = Lblk[(int64_t)min(i, b - 1) * lds + min(j, b - 1)];
         v[t] = (i < b && j <= i) ? x : (i == j ? 1.0f : 0.0f);
       }
 #pragma unroll
@@ -609,6 +610,16 @@ __device__ __forceinline__ void leaf_body(LeafLDS& sm, const float* Lblk, float*
   }
 }
 
+// Factorisation and inverse of a factor of one block (dim <= 128), read from
+// where it is (F, leading dimension dim): no work copy, no panels.
+__global__ __launch_bounds__(256) void k_chol_single(const float* F, float* __restrict__ L,
+                                                     float* __restrict__ Li, int dim, int64_t ld,
+                                                     double* logdet, int iteration, int side, int* st) {
+  if (ff_halted(st)) return;
+  __shared__ LeafLDS sm;
+  leaf_body(sm, F, Li, ld, dim, 0, logdet, 0, iteration, side, st, L, nullptr, dim);
+}
+
 // Trailing-update tile of a right-looking step: the two 128-row blocks of
 // the panel (columns ok.., rows i0.. and j0..) in LDS.
 struct TrailLDS {
@@ -637,7 +648,7 @@ __global__ __launch_bounds__(256) void k_chol_step(float* __restrict__ L, float*
     const int b = (int)min<int64_t>(NB, dim - d0);
     float* Akk = L + d0 * ld + d0;
     leaf_body(sm.leaf, Akk, Li + d0 * ld + d0, ld, b, d0, logdet, (int)(d0 / NB), iteration, side,
-              st, Akk, ok >= 0 ? L + d0 * ld + ok : nullptr);
+              st, Akk, ok >= 0 ? L + d0 * ld + ok : nullptr, ld);
     return;
   }
   const int64_t R = (dim - d0 + NB - 1) / NB;   // block rows at or below d0
@@ -787,6 +798,14 @@ hipError_t launch_chol_step(float* L, float* Li, int64_t dim, int64_t ld, int64_
   const int64_t grid = 1 + std::min<int64_t>(ntiles, kStepWorkers);
   hipLaunchKernelGGL(k_chol_step, dim3((uint32_t)grid), dim3(256), 0, s, L, Li, dim, ld, d0,
                      ok >= 0 ? ok : (int64_t)-1, jend, logdet, iteration, side, st);
+  return hipGetLastError();
+}
+
+hipError_t launch_chol_single(const float* F, float* L, float* Li, int64_t dim, int64_t ld,
+                              double* logdet, int iteration, int side, int* st, hipStream_t s) {
+  if (dim < 1 || dim > kLeaf || ld < dim) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_chol_single, dim3(1), dim3(256), 0, s, F, L, Li, (int)dim, ld, logdet, iteration,
+                     side, st);
   return hipGetLastError();
 }
 

@@ -455,16 +455,19 @@ ff_status inverse_p1_split(ff_handle_s* h, Side& s, int64_t o, int64_t sz, int64
 // after the last leaf is the factorisation's tail.  The upper triangle of
 // s.L is scratch.
 constexpr int64_t kInvEvery = 8;
+constexpr int64_t kOneStream = 3;
 constexpr int64_t kOuter = 2048;
 
 ff_status chol_blocked(ff_handle_s* h, Side& s, int iteration) {
-  // One stream (h->single_stream): the inverse products go on the main
-  // stream in the same order, after the panels they need.
-  const bool two = !h->single_stream;
-  ff_status rc = two ? side_streams(s) : FF_OK;
-  if (rc != FF_OK) return rc;
   const int64_t d = s.dim, ld = s.ld;
   const int64_t nb = (d + kLeaf - 1) / kLeaf;
+  // One stream (h->single_stream, or few leaves): the inverse products go on
+  // the main stream in the same order, after the panels they need.  Handing
+  // a product to the second stream costs the main one about as long as a
+  // small product takes (6 us for the event, 20 for the join at the end).
+  const bool two = !h->single_stream && nb > kOneStream;
+  ff_status rc = two ? side_streams(s) : FF_OK;
+  if (rc != FF_OK) return rc;
   const int64_t outer = d > kTwoLevel ? kOuter : nb * kLeaf;
   hipStream_t ms = h->stream;
   hipStream_t is = two ? s.istream : ms;
@@ -563,12 +566,17 @@ double samples_per_dim(const ff_handle_s* h) {
 // s.Lw; sum log L_jj per leaf into s.slots.
 ff_status cholinv_from(ff_handle_s* h, Side& s, const float* src, int iteration) {
   Timed t(h, 3, (double)s.dim * s.dim * s.dim / 3.0);
-  if (s.ld == s.dim)
-    FF_HIP(launch_copy_f32(src, s.L, s.dim * s.dim, h->st, h->stream));
-  else
-    FF_HIP(launch_copy2d_f32(src, s.dim, s.L, s.ld, s.dim, s.dim, h->st, h->stream));
-  ff_status rc = chol_blocked(h, s, iteration);
-  if (rc != FF_OK) return rc;
+  if (s.dim <= kLeaf) {
+    FF_HIP(launch_chol_single(src, s.L, s.Li, s.dim, s.ld, s.slots, iteration, s.code, h->st, h->stream));
+  } else {
+    if (s.ld == s.dim)
+      FF_HIP(launch_copy_f32(src, s.L, s.dim * s.dim, h->st, h->stream));
+    else
+      FF_HIP(launch_copy2d_f32(src, s.dim, s.L, s.ld, s.dim, s.dim, h->st, h->stream));
+    ff_status rc = chol_blocked(h, s, iteration);
+    if (rc != FF_OK) return rc;
+  }
+  if (s.Lw == (void*)s.Li) return FF_OK;  // the operand is the inverse itself
   FF_HIP(launch_convert_inverse(s.Li, s.dim, s.ld, s.Lw, s.Lw2, s.dim_p, h->elem, src, s.spart, h->st,
                                 h->stream));
   if (s.split_flag != nullptr) {
@@ -687,6 +695,14 @@ ff_status token_weights(ff_handle_s* h, Side& p, float* wbuf, bool identity = fa
   return FF_OK;
 }
 
+// Damping and trace of a new factor.  Only A's trace is used (the
+// normalisation), so B without damping needs neither.
+ff_status finish_update(ff_handle_s* h, Side& s, float* F) {
+  if (h->cfg.damping > 0.0 || &s == &h->A)
+    FF_HIP(launch_trace_damp(F, s.dim, h->cfg.damping, s.tr, h->st, h->stream));
+  return FF_OK;
+}
+
 // Rank-one form of the half step (Section 5): s.F[slot] =
 // (1/(N p.dim)) sum_t ||L_p^-1 v_t||^2 u_t u_t^T with u_t the token vector of
 // side s, as a symmetric product over tokens of the weighted, transposed u.
@@ -736,8 +752,7 @@ ff_status update_rank1(ff_handle_s* h, Side& s, Side& p, int slot, bool finish,
     Timed t(h, 2, 0.0);
     FF_HIP(launch_reduce_rowmajor(h->P, s.splits, s.dim_p, F, s.dim, scale, h->st, h->stream));
   }
-  if (finish) FF_HIP(launch_trace_damp(F, s.dim, h->cfg.damping, s.tr, h->st, h->stream));
-  return FF_OK;
+  return finish ? finish_update(h, s, F) : FF_OK;
 }
 
 // s.F[slot] (or dst) = (1/(N p.dim)) sum_i X_i Li_p^T Li_p X_i^T  (+ damping), trace into
@@ -805,8 +820,7 @@ ff_status update(ff_handle_s* h, Side& s, Side& p, int slot, bool finish = true,
       FF_HIP(launch_reduce_rowmajor(h->P, s.splits, s.dim_p, F, s.dim, scale, h->st, h->stream));
     }
   }
-  if (finish) FF_HIP(launch_trace_damp(F, s.dim, h->cfg.damping, s.tr, h->st, h->stream));
-  return FF_OK;
+  return finish ? finish_update(h, s, F) : FF_OK;
 }
 
 ff_status read_status(ff_handle_s* h, int st[4]) {
@@ -1050,7 +1064,9 @@ ff_status init_handle(const ff_config* cfg, const Layout& lay, ff_handle_s* h) {
     s.F[1] = (float*)(ws + o[1]);
     s.L = (float*)(ws + o[2]);
     s.Li = (float*)(ws + o[3]);
-    s.Lw = ws + o[4];
+    // fp32 and no padding: the flip-flop's whitening operand is L^-1 itself
+    // (the other estimators put other matrices there)
+    s.Lw = !h->bf16 && dim_p == dim && cfg->estimator == FF_EST_FLIPFLOP ? (void*)s.Li : (void*)(ws + o[4]);
     s.Lw2 = h->bf16 && h->cfg.whiten_split != 1 ? (void*)(ws + o[5]) : nullptr;
     if (h->bf16 && h->cfg.whiten_split == 0) {
       const int64_t dmax = std::max(lay.m_p, lay.n_p);

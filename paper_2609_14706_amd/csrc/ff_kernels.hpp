@@ -116,6 +116,11 @@ hipError_t launch_panel_solve(float* P, const float* Xkk, int64_t ld, int64_t ro
 hipError_t launch_chol_step(float* L, float* Li, int64_t dim, int64_t ld, int64_t d0, int64_t ok,
                             int64_t jend, double* logdet, int iteration, int side, int* st, hipStream_t s);
 
+// Factor of one block, dim <= 128: F (leading dimension dim) -> L and L^-1
+// (leading dimension ld), otherwise as launch_chol_step's diagonal block.
+hipError_t launch_chol_single(const float* F, float* L, float* Li, int64_t dim, int64_t ld,
+                              double* logdet, int iteration, int side, int* st, hipStream_t s);
+
 // out[s][r][c] (rows_p x cols_p) from G[s] (m x n): copy (transpose = 0,
 // rows_p >= m, cols_p >= n) or transpose (transpose = 1, rows_p >= n,
 // cols_p >= m), zero padding.  elem_bytes = 2 (bf16) or 4 (fp32).
