@@ -17,6 +17,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <mutex>
 #include <new>
 #include <string>
@@ -72,7 +73,7 @@ struct Side {
   bool lw_valid = false;             // Lw holds the inverse factor of F[cur]
   bool start_identity = false;       // the starting factor is I (no A0 / B0 given)
   int code = 0;                      // 1 = A, 2 = B
-  // second stream of the blocked factorisation (created on first use): it
+  // second stream of the blocked factorisation (taken on first use): it
   // builds the off-diagonal blocks of the inverse
   hipStream_t istream = nullptr;
   hipEvent_t ev_leaf = nullptr, ev_inv = nullptr;
@@ -334,13 +335,61 @@ void collect_timing(ff_handle_s* h) {
 }
 
 // ------------------------------------------------------- factorisation
-ff_status side_streams(Side& s) {
-  if (s.istream == nullptr) {
-    FF_HIP(hipStreamCreateWithFlags(&s.istream, hipStreamNonBlocking));
-    FF_HIP(hipEventCreateWithFlags(&s.ev_leaf, hipEventDisableTiming));
-    FF_HIP(hipEventCreateWithFlags(&s.ev_inv, hipEventDisableTiming));
+// Second streams (with their two events) of destroyed handles, kept for the
+// next ones: a fit's two cost 0.15 to 0.2 ms to create and destroy.  A set
+// belongs to one Side from take to give; at most kIdleSets wait here, more are
+// destroyed.  A given set's stream is idle: its last work is waited for by
+// the handle's stream, which ff_destroy synchronises first.
+struct StreamSet {
+  int device;
+  hipStream_t stream;
+  hipEvent_t leaf, inv;
+};
+constexpr size_t kIdleSets = 8;
+std::mutex g_sets_mu;
+std::vector<StreamSet>& idle_sets() {  // never destroyed: no HIP call at process exit
+  static std::vector<StreamSet>* sets = new std::vector<StreamSet>();
+  return *sets;
+}
+
+ff_status take_side_streams(Side& s, int device) {
+  if (s.istream != nullptr) return FF_OK;
+  {
+    std::lock_guard<std::mutex> lock(g_sets_mu);
+    std::vector<StreamSet>& idle = idle_sets();
+    for (size_t k = 0; k < idle.size(); ++k)
+      if (idle[k].device == device) {
+        s.istream = idle[k].stream;
+        s.ev_leaf = idle[k].leaf;
+        s.ev_inv = idle[k].inv;
+        idle.erase(idle.begin() + (std::ptrdiff_t)k);
+        return FF_OK;
+      }
   }
+  FF_HIP(hipStreamCreateWithFlags(&s.istream, hipStreamNonBlocking));
+  FF_HIP(hipEventCreateWithFlags(&s.ev_leaf, hipEventDisableTiming));
+  FF_HIP(hipEventCreateWithFlags(&s.ev_inv, hipEventDisableTiming));
   return FF_OK;
+}
+
+void give_side_streams(Side& s, int device) {
+  if (s.istream == nullptr) return;
+  // a set that is whole and whose stream ended without an error is kept
+  if (hipStreamSynchronize(s.istream) == hipSuccess && s.ev_leaf != nullptr && s.ev_inv != nullptr) {
+    std::lock_guard<std::mutex> lock(g_sets_mu);
+    if (idle_sets().size() < kIdleSets) {
+      try {
+        idle_sets().push_back(StreamSet{device, s.istream, s.ev_leaf, s.ev_inv});
+        s.istream = nullptr;
+        return;
+      } catch (...) {  // no room to remember it
+      }
+    }
+  }
+  (void)hipStreamDestroy(s.istream);
+  if (s.ev_leaf != nullptr) (void)hipEventDestroy(s.ev_leaf);
+  if (s.ev_inv != nullptr) (void)hipEventDestroy(s.ev_inv);
+  s.istream = nullptr;
 }
 
 constexpr int64_t kTwoLevel = 6144;  // wider factors go in outer panels (see chol_blocked)
@@ -466,7 +515,7 @@ ff_status chol_blocked(ff_handle_s* h, Side& s, int iteration) {
   // a product to the second stream costs the main one about as long as a
   // small product takes (6 us for the event, 20 for the join at the end).
   const bool two = !h->single_stream && nb > kOneStream;
-  ff_status rc = two ? side_streams(s) : FF_OK;
+  ff_status rc = two ? take_side_streams(s, h->device) : FF_OK;
   if (rc != FF_OK) return rc;
   const int64_t outer = d > kTwoLevel ? kOuter : nb * kLeaf;
   hipStream_t ms = h->stream;
@@ -1637,14 +1686,7 @@ ff_status ff_destroy(ff_handle h) {
     (void)hipEventDestroy(h->fork);
     (void)hipEventDestroy(h->join);
   }
-  for (Side* sd : {&h->A, &h->B}) {
-    if (sd->istream != nullptr) {
-      (void)hipStreamSynchronize(sd->istream);
-      (void)hipStreamDestroy(sd->istream);
-      (void)hipEventDestroy(sd->ev_leaf);
-      (void)hipEventDestroy(sd->ev_inv);
-    }
-  }
+  for (Side* sd : {&h->A, &h->B}) give_side_streams(*sd, h->device);
   for (hipEvent_t e : h->events) (void)hipEventDestroy(e);
   delete h;
   return FF_OK;
