@@ -365,20 +365,28 @@ __global__ __launch_bounds__(NTHR, 1) void k_whiten_bf16(const bf16_t* __restric
                                                          const bf16_t* __restrict__ Y2,
                                                          const int* __restrict__ use2, const int* __restrict__ use2b,
                                                          bf16_t* __restrict__ C, uint32_t Kp,
-                                                         uint32_t full, const int* st) {
+                                                         uint32_t full, uint32_t single, const int* st) {
   if (ff_halted(st)) return;
   if (one_pass(use2, use2b)) Y2 = nullptr;
   __shared__ Ring sm;
   const uint32_t ncol = Kp / TM, npair = (ncol + 1) / 2;
   uint32_t rb, c;
-  whiten_item(xcd_remap(blockIdx.x, gridDim.x), gridDim.x / npair, npair, rb, c);
+  if (single) {  // one tile a workgroup, the longest first
+    const uint32_t nrb = gridDim.x / ncol;
+    rb = blockIdx.x % nrb;
+    c = ncol - 1 - blockIdx.x / nrb;
+  } else {
+    whiten_item(xcd_remap(blockIdx.x, gridDim.x), gridDim.x / npair, npair, rb, c);
+  }
   const bf16_t* xa = X + (size_t)rb * TM * Kp;
   Acc acc;
   zero_acc(acc);
-  const WhitenAddr a0 = whiten_addr(xa, Y, Y2, c, false, Kp, full != 0);
+  // (a pair's second tile runs through k backwards; alone it does so too, for
+  // the same sums)
+  const WhitenAddr a0 = whiten_addr(xa, Y, Y2, c, single != 0 && 2 * c >= ncol, Kp, full != 0);
   mainloop<false, true, false>(sm, 0, a0.pairs(), Kp, Kp, a0, acc);
   store_whitened(acc, C, rb, c, Kp);
-  if (ncol - 1 - c != c) {
+  if (!single && ncol - 1 - c != c) {
     // the second tile's first copies go out right behind the first tile's
     // stores, so that their latency overlaps the stores' drain
     const uint32_t cj = ncol - 1 - c;
@@ -578,10 +586,15 @@ hipError_t launch_whiten_bf16(const bf16_t* X, const bf16_t* Y, const bf16_t* Y2
                               hipStream_t s, bool full) {
   // Kp <= 2^20 keeps every copy's byte offset from its pair base below 2^31
   if (rows <= 0 || Kp <= 0 || rows % TM || Kp % TM || Kp > (1 << 20)) return hipErrorInvalidValue;
-  const int64_t tiles = (rows / TM) * ((Kp / TM + 1) / 2);  // one workgroup per tile pair
+  // one workgroup per tile pair, or per tile when all tiles fit on the GPU at
+  // once (a 512-wide operand's pair runs for three column tiles' k, its longest
+  // tile for two: 48 -> 36 us at 64 row blocks, two passes)
+  const int64_t ncol = Kp / TM;
+  const bool single = rows / TM * ncol <= 256;
+  const int64_t tiles = (rows / TM) * (single ? ncol : (ncol + 1) / 2);
   if (tiles > 0x7fffffff) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_whiten_bf16, dim3((uint32_t)tiles), dim3(NTHR), 0, s, X, Y, Y2, use2, use2b, C,
-                     (uint32_t)Kp, (uint32_t)full, st);
+                     (uint32_t)Kp, (uint32_t)full, (uint32_t)single, st);
   return hipGetLastError();
 }
 
