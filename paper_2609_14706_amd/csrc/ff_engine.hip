@@ -334,6 +334,17 @@ void collect_timing(ff_handle_s* h) {
   h->ev_used = 0;
 }
 
+ff_status read_status(ff_handle_s* h, int st[4]) {
+  FF_HIP(hipMemcpyAsync(st, h->st, 4 * sizeof(int), hipMemcpyDeviceToHost, h->stream));
+  FF_HIP(hipStreamSynchronize(h->stream));
+  return FF_OK;
+}
+
+ff_status clear_status(ff_handle_s* h) {
+  FF_HIP(launch_set_int(h->st, 4, 0, h->stream));
+  return FF_OK;
+}
+
 // ------------------------------------------------------- factorisation
 // Second streams (with their two events) of destroyed handles, kept for the
 // next ones: a fit's two cost 0.15 to 0.2 ms to create and destroy.  A set
@@ -640,6 +651,56 @@ ff_status cholinv(ff_handle_s* h, Side& s, int slot, int iteration) {
   return cholinv_from(h, s, s.F[slot], iteration);
 }
 
+// The handle's second main stream and its events, created on first use.
+ff_status aux_stream(ff_handle_s* h) {
+  if (h->aux != nullptr) return FF_OK;
+  FF_HIP(hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking));
+  FF_HIP(hipEventCreateWithFlags(&h->fork, hipEventDisableTiming));
+  FF_HIP(hipEventCreateWithFlags(&h->join, hipEventDisableTiming));
+  return FF_OK;
+}
+
+// fA() with the work it enqueues on the handle's stream, fB() on the second
+// one, forked from the handle's stream and joined back into it: A's and B's
+// factorisations are independent and latency bound (a 4096 pair 3.6 ms one
+// after the other, 2.6 side by side).
+template <class FA, class FB>
+ff_status side_by_side(ff_handle_s* h, const FA& fA, const FB& fB) {
+  ff_status rc = aux_stream(h);
+  if (rc != FF_OK) return rc;
+  FF_HIP(hipEventRecord(h->fork, h->stream));
+  FF_HIP(hipStreamWaitEvent(h->aux, h->fork, 0));
+  if ((rc = fA()) != FF_OK) return rc;
+  const hipStream_t main = h->stream;
+  h->stream = h->aux;
+  rc = fB();
+  h->stream = main;
+  if (rc != FF_OK) return rc;
+  FF_HIP(hipEventRecord(h->join, h->aux));
+  FF_HIP(hipStreamWaitEvent(h->stream, h->join, 0));
+  return FF_OK;
+}
+
+// L^-1 of both factors (label -1: not part of an iteration).
+ff_status cholinv_both(ff_handle_s* h, const float* Af, const float* Bf) {
+  return side_by_side(h, [&] { return cholinv_from(h, h->A, Af, -1); },
+                      [&] { return cholinv_from(h, h->B, Bf, -1); });
+}
+
+// After cholinv_both failed: the error for the factor to blame, A if it is
+// not positive definite (both may not be, and the two streams' failures come
+// in any order), with the status cleared.
+ff_status blame_factor(ff_handle_s* h, const float* Af, const char* where) {
+  ff_status rc = clear_status(h);
+  if (rc != FF_OK || (rc = cholinv_from(h, h->A, Af, -1)) != FF_OK) return rc;
+  int st[4];
+  if ((rc = read_status(h, st)) != FF_OK) return rc;
+  if ((rc = clear_status(h)) != FF_OK) return rc;
+  FF_HIP(hipStreamSynchronize(h->stream));
+  return fail(FF_ERR_NOT_SPD, std::string("factor ") + (st[0] != 0 ? "A" : "B") +
+                                  " not positive definite in " + where);
+}
+
 // Frobenius estimator: the half steps B = (1/(N n)) sum_i G_i A G_i^T and
 // A = (1/(N m)) sum_i G_i^T B G_i use the factor itself, so the operand is F
 // rounded to the samples' type (dense, both triangles; hi + lo parts with
@@ -870,17 +931,6 @@ ff_status update(ff_handle_s* h, Side& s, Side& p, int slot, bool finish = true,
     }
   }
   return finish ? finish_update(h, s, F) : FF_OK;
-}
-
-ff_status read_status(ff_handle_s* h, int st[4]) {
-  FF_HIP(hipMemcpyAsync(st, h->st, 4 * sizeof(int), hipMemcpyDeviceToHost, h->stream));
-  FF_HIP(hipStreamSynchronize(h->stream));
-  return FF_OK;
-}
-
-ff_status clear_status(ff_handle_s* h) {
-  FF_HIP(launch_set_int(h->st, 4, 0, h->stream));
-  return FF_OK;
 }
 
 // Relative change of A (x) B between the iterate in `slot` and the one
@@ -1427,9 +1477,8 @@ ff_status ff_kron_apply(ff_handle h, const float* X, float* Y, int64_t batch, ff
   const int cur = h->cur;
   ff_status rc;
   if (mode == FF_APPLY_INV) {
-    // Fresh factorisations of the current factors (label 0 marks them).
-    if ((rc = cholinv(h, h->A, cur, -1)) != FF_OK) return rc;
-    if ((rc = cholinv(h, h->B, cur, -1)) != FF_OK) return rc;
+    // Fresh factorisations of the current factors.
+    if ((rc = cholinv_both(h, h->A.F[cur], h->B.F[cur])) != FF_OK) return rc;
     // the cached whitening operands of the other estimators are now stale
     if (h->cfg.estimator != FF_EST_FLIPFLOP) h->A.lw_valid = h->B.lw_valid = false;
   }
@@ -1471,11 +1520,8 @@ ff_status ff_kron_apply(ff_handle h, const float* X, float* Y, int64_t batch, ff
   int st[4];
   if ((rc = read_status(h, st)) != FF_OK) return rc;
   if (st[0] != 0) {
-    if ((rc = clear_status(h)) != FF_OK) return rc;
-    FF_HIP(hipStreamSynchronize(h->stream));
     h->A.lw_valid = h->B.lw_valid = false;
-    return fail(FF_ERR_NOT_SPD, std::string("factor ") + (st[1] == 1 ? "A" : "B") +
-                                    " not positive definite in ff_kron_apply");
+    return blame_factor(h, h->A.F[cur], "ff_kron_apply");
   }
   return FF_OK;
 }
@@ -1489,8 +1535,7 @@ ff_status ff_objective(ff_handle h, const float* A, const float* B, double* psi)
   // The whitening operands no longer belong to the current factors.
   h->A.lw_valid = h->B.lw_valid = false;
   ff_status rc;
-  if ((rc = cholinv_from(h, h->A, Af, -1)) != FF_OK) return rc;
-  if ((rc = cholinv_from(h, h->B, Bf, -1)) != FF_OK) return rc;
+  if ((rc = cholinv_both(h, Af, Bf)) != FF_OK) return rc;
   if (h->lay.rank1) {
     // tr(B^-1 g x^T A^-1 x g^T) = (x^T A^-1 x)(g^T B^-1 g): a dot of token weights
     float* w = h->wv;
@@ -1505,12 +1550,7 @@ ff_status ff_objective(ff_handle h, const float* A, const float* B, double* psi)
     FF_HIP(hipMemcpyAsync(terms, out, sizeof terms, hipMemcpyDeviceToHost, h->stream));
     int st[4];
     if ((rc = read_status(h, st)) != FF_OK) return rc;
-    if (st[0] != 0) {
-      if ((rc = clear_status(h)) != FF_OK) return rc;
-      FF_HIP(hipStreamSynchronize(h->stream));
-      return fail(FF_ERR_NOT_SPD, std::string("factor ") + (st[1] == 1 ? "A" : "B") +
-                                      " not positive definite in ff_objective");
-    }
+    if (st[0] != 0) return blame_factor(h, Af, "ff_objective");
     const double mn = (double)h->m * (double)h->n;
     *psi = log(terms[0] / ((double)h->N * mn)) + terms[1] / (double)h->n + terms[2] / (double)h->m;
     return FF_OK;
@@ -1538,12 +1578,7 @@ ff_status ff_objective(ff_handle h, const float* A, const float* B, double* psi)
   FF_HIP(hipMemcpyAsync(terms, out, sizeof terms, hipMemcpyDeviceToHost, h->stream));
   int st[4];
   if ((rc = read_status(h, st)) != FF_OK) return rc;
-  if (st[0] != 0) {
-    if ((rc = clear_status(h)) != FF_OK) return rc;
-    FF_HIP(hipStreamSynchronize(h->stream));
-    return fail(FF_ERR_NOT_SPD, std::string("factor ") + (st[1] == 1 ? "A" : "B") +
-                                    " not positive definite in ff_objective");
-  }
+  if (st[0] != 0) return blame_factor(h, Af, "ff_objective");
   // (1/(N m n)) sum_i tr(B^-1 G_i A^-1 G_i^T) = tr(B^-1 M) / m
   *psi = log(terms[0] / (double)m) + terms[1] / (double)h->n + terms[2] / (double)m;
   return FF_OK;
@@ -1601,25 +1636,15 @@ ff_status ff_quantize(ff_handle h, const float* W, const float* A, const float* 
   ff_status rc;
   // The two factorisations are independent and latency bound: B's runs on a
   // second stream, forked from and joined back into the handle's stream.
-  if (h->aux == nullptr) {
-    FF_HIP(hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking));
-    FF_HIP(hipEventCreateWithFlags(&h->fork, hipEventDisableTiming));
-    FF_HIP(hipEventCreateWithFlags(&h->join, hipEventDisableTiming));
-  }
-  FF_HIP(hipEventRecord(h->fork, h->stream));
-  FF_HIP(hipStreamWaitEvent(h->aux, h->fork, 0));
-  if ((rc = quant_side(h, h->A, A != nullptr ? A : h->A.F[cur], q.nq, La, dA, gamma, given, alpha,
-                       al)) != FF_OK)
-    return rc;
-  {
-    const hipStream_t main = h->stream;
-    h->stream = h->aux;
-    rc = quant_side(h, h->B, B != nullptr ? B : h->B.F[cur], q.mq, Lb, dB, gamma, given, beta, be);
-    h->stream = main;
-    if (rc != FF_OK) return rc;
-  }
-  FF_HIP(hipEventRecord(h->join, h->aux));
-  FF_HIP(hipStreamWaitEvent(h->stream, h->join, 0));
+  rc = side_by_side(
+      h,
+      [&] {
+        return quant_side(h, h->A, A != nullptr ? A : h->A.F[cur], q.nq, La, dA, gamma, given, alpha, al);
+      },
+      [&] {
+        return quant_side(h, h->B, B != nullptr ? B : h->B.F[cur], q.mq, Lb, dB, gamma, given, beta, be);
+      });
+  if (rc != FF_OK) return rc;
   int st[4];
   if ((rc = read_status(h, st)) != FF_OK) return rc;
   if (st[0] != 0) {

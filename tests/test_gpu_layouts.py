@@ -111,3 +111,26 @@ def test_noalloc_at_its_scratch_limit(gpu):
     f.close()
     assert done == 2 and np.allclose(ll, want, rtol=1e-12)
     assert torch.equal(A, FA) and torch.equal(B, FB)
+
+
+@pytest.mark.parametrize("bad", ["A", "B", "AB"])
+def test_which_factor_is_blamed(gpu, bad):
+    """Both factorisations run side by side: the error names A if A is not
+    positive definite, whichever failed first, and the handle stays usable."""
+    m, n = 300, 150
+    A, B = _spd(n, 1), _spd(m, 2)
+    A2, B2 = A.clone(), B.clone()
+    if "A" in bad:
+        A2[140, 140] = -1.0
+    if "B" in bad:
+        B2[3, 3] = -1.0
+    f = ffe.FlipFlop(_samples(4, m, n).to(gpu), A0=A2.to(gpu), B0=B2.to(gpu), damping=0.1)
+    X = torch.randn(1, m, n, device=gpu)
+    for call in (lambda: f.kron_apply(X, inverse=True), f.objective):
+        with pytest.raises(ffe.FlipFlopError) as e:
+            call()
+        assert e.value.code == ffe.FF_ERR_NOT_SPD and f"factor {bad[0]} not positive" in str(e.value)
+    psi = f.objective(A.to(gpu), B.to(gpu))
+    want = oracle.objective(_samples(4, m, n).numpy(), A.double().numpy(), B.double().numpy())
+    assert abs(psi - want) < 1e-5
+    f.close()
