@@ -1,10 +1,10 @@
 // General fp32 product on the fp32 matrix cores (v_mfma_f32_32x32x2_f32).
 //
 // The smaller fp32 products: the tree of the triangular inverse of a factor,
-// small fp32 layers.  64 x 64 output tiles, four waves of one 32 x 32
+// smaller fp32 layers.  64 x 64 output tiles, four waves of one 32 x 32
 // matrix-core tile, 64-wide k slices staged through double-buffered LDS (such
-// products are latency bound: few, large slices).  Products that give the
-// GPU 256 tiles of 128 x 128 or more go to ff_gemm_split.hip.  Any shape and
+// products are latency bound: few, large slices).  Products that fill the GPU
+// with larger tiles go to ff_gemm_split.hip.  Any shape and
 // either operand transpose; k ranges can be clipped to the non-zero triangle
 // of a triangular operand, k can run over segments (the stacked samples), and
 // k can be split over the grid into partial outputs.  When every operand is
@@ -286,14 +286,19 @@ hipError_t launch_gemm_f32(const GemmF32& p, int batch, hipStream_t s) {
                    (!segmented || (p.kseg % 4 == 0 && p.segA % 4 == 0 && p.segB % 4 == 0));
   GemmF32 q = p;
   if (!segmented) q.kseg = 0;  // plain k axis: the kernels skip the segment arithmetic
-  // From 256 tiles of 128 x 128 (128 of the split kernel's 256 x 128, half
-  // the CUs) the three-part products win: 4096 x 4096 x 4096 triangular 0.41 ms
-  // against 0.65 on the fp32 matrix cores (128 x 128 tiles); below, four times
-  // as many 64 x 64 tiles fill the GPU better.
+  // The three-part products win once they fill enough of the GPU, counted in
+  // tiles of 128 x 128 (half a 256 x 128 tile each); below, 64 x 64 tiles fill
+  // it better.  Four pairs of dense products (B X A): 196 tiles (1792 x 1792)
+  // 1.19 ms against 1.38, 169 (1600 x 1600) 1.07 against 1.01.  With a triangular
+  // operand (and more than one tile along its index) the longest tiles finish
+  // alone, the more so the fewer there are: four inverse applications with
+  // 441 tiles (2600 x 2600) 5.1 ms against 6.3, 324 (2304 x 2304) 4.3 against 3.9.
   const int64_t big_tiles = ((p.M + 127) / 128) * ((p.N + 127) / 128) *
                             (p.ksplit > 1 ? p.ksplit : batch);
   const bool square = !(p.flags & kCLower) || p.M == p.N;
-  if (p.tile != 64 && big_tiles >= 256 && square && p.lda <= kSplitMaxLd && p.ldb <= kSplitMaxLd)
+  const bool tri = ((p.flags & (kKHiRow | kKLoRow)) && p.M > 128) ||
+                   ((p.flags & (kKHiCol | kKLoCol)) && p.N > 128);
+  if (p.tile != 64 && big_tiles >= (tri ? kSplitMinTri : kSplitMinDense) && square && p.lda <= kSplitMaxLd && p.ldb <= kSplitMaxLd)
     return launch_gemm_split(q, batch, vec, deep, s);
   return launch_tiles(q, batch, vec, deep, s);
 }

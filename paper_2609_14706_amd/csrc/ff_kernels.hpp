@@ -86,6 +86,8 @@ hipError_t launch_gemm_f32(const GemmF32& p, int batch, hipStream_t s);
 // divisible by 4.  deep: k per workgroup beyond 16384.  With kCLower M = N;
 // lda, ldb <= kSplitMaxLd (32-bit offsets within a tile's slice).
 constexpr int64_t kSplitMaxLd = 1 << 23;
+// Tiles of 128 x 128 from which launch_gemm_f32 takes it (reasons there).
+constexpr int64_t kSplitMinDense = 192, kSplitMinTri = 400;
 hipError_t launch_gemm_split(const GemmF32& p, int batch, bool vec, bool deep, hipStream_t s);
 
 // F (dim x dim) = scale * sum_z P[z] with P[z] row-major dim_p x dim_p, lower

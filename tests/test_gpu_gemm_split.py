@@ -1,7 +1,7 @@
 """The large fp32 products (three bf16 parts per entry, csrc/ff_gemm_split.hip)
-through ff_kron_apply, which takes them once a product has 256 tiles of
-128 x 128: at tile edges and remainders, both operand layouts, triangular
-operands, against fp64."""
+through ff_kron_apply, which takes them once a launch has 192 tiles of
+128 x 128 (400 with a triangular operand of more than one tile): at tile edges
+and remainders, both operand layouts, triangular operands, against fp64."""
 import math
 
 import numpy as np
@@ -20,9 +20,10 @@ def _spd(d, seed):
     return (Q @ Q.T / d + torch.eye(d, dtype=torch.float64)).float()
 
 
-def _handle(m, n):
+def _handle(m, n, batch):
     A, B = _spd(n, 1), _spd(m, 2)
-    G = torch.zeros(1, m, n, device="cuda")
+    # as many samples as matrices to apply: the workspace then takes the whole batch in one launch
+    G = torch.zeros(batch, m, n, device="cuda")
     return ffe.FlipFlop(G, A0=A.cuda(), B0=B.cuda()), A.double(), B.double()
 
 
@@ -34,7 +35,7 @@ SHAPES = [(255, 127, 260), (256, 128, 256), (36, 33, 300), (1, 130, 256), (257, 
 
 @pytest.mark.parametrize("m,n,batch", SHAPES)
 def test_products_against_fp64(m, n, batch):
-    f, A, B = _handle(m, n)
+    f, A, B = _handle(m, n, batch)
     X = torch.randn(batch, m, n, generator=torch.Generator().manual_seed(3))
     Y = f.kron_apply(X.cuda()).cpu().double()
     Xd = X.double()
@@ -52,7 +53,7 @@ def test_products_against_fp64(m, n, batch):
 
 @pytest.mark.parametrize("m,n,batch", [(127, 129, 260), (256, 260, 70), (36, 33, 300)])
 def test_triangular_products_against_fp64(m, n, batch):
-    f, A, B = _handle(m, n)
+    f, A, B = _handle(m, n, batch)
     X = torch.randn(batch, m, n, generator=torch.Generator().manual_seed(4))
     Y = f.kron_apply(X.cuda(), inverse=True).cpu().double()
     ref = torch.linalg.solve(B, X.double()) @ torch.linalg.inv(A)
@@ -65,7 +66,7 @@ def test_extreme_values():
     """Infinities, NaNs, values that round to a bf16 infinity, tiny values:
     as in an fp32 product with dense operands."""
     m, n, batch = 128, 132, 256
-    f, A, B = _handle(m, n)
+    f, A, B = _handle(m, n, batch)
     X = torch.randn(batch, m, n, generator=torch.Generator().manual_seed(5))
     X[3, 5, 7] = math.inf
     X[4, 6, 8] = -math.inf
