@@ -32,6 +32,7 @@ namespace {
 constexpr int BM = 256, BN = 128;  // tile rows and columns
 constexpr int BK = 32;             // k per slice
 constexpr int CHUNK = 32;          // slices per fresh accumulator (DEEP)
+constexpr int FP32_CHUNK = 8;      // the same of fp32 products
 constexpr int ROWB = BK * 2;       // bytes of a row of one part in LDS
 constexpr int PA = BM * ROWB, PB = BN * ROWB;  // bytes of one part of an operand slice
 constexpr int BUF = 3 * (PA + PB);             // bytes of a slice's parts
@@ -46,7 +47,7 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 // rows, one chunk) cover all banks.
 struct __align__(16) SplitLDS {
   char p[2 * BUF];
-  int wide;  // set once an entry does not fit the split (infinite, or near the largest float)
+  int wide;  // set once the tile has to be computed from the fp32 numbers
 };
 
 // LDS row of column o of the second operand: within each 64-column half,
@@ -76,8 +77,8 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {  // round to neare
 
 // Entries above this magnitude (or infinite) set SplitLDS::wide: an infinity
 // would meet the zero or opposite parts of finite factors and turn into NaN.
-// The tile is then computed again from fp32 numbers, h + m + l each, on the
-// fp32 matrix cores, as is a last slice of fewer than 32 k.
+// The tile is then computed again from the fp32 numbers themselves on the
+// fp32 matrix cores (fp32_slice), as is a last slice of fewer than 32 k.
 constexpr float kWide = 3.3895313e38f;
 
 // A thread's share of a slice: groups of eight consecutive k of one row of
@@ -117,6 +118,13 @@ struct Split {
     }
   }
 };
+
+// A slice of fp32 numbers in LDS: rows of 128 bytes, the first operand's 256,
+// then the second's 128 (col_row); a row's 16-byte chunk c (4 k) sits at
+// position c ^ (row & 7).
+__device__ __forceinline__ uint32_t fp32_at(int row, int c) {
+  return (uint32_t)row * (BK * 4) + 16u * (uint32_t)(c ^ (row & 7));
+}
 
 template <bool AK, bool BKM, bool VEC>
 struct Stage {
@@ -166,11 +174,26 @@ struct Stage {
     const int64_t k = k0 + 8 * (is_a ? chunk_a<AK>(g, tid) : chunk_b<BKM>(g - 4, tid));
     const float* P = is_a ? A : B;
     const int64_t ld = is_a ? p.lda : p.ldb, seg = is_a ? p.segA : p.segB;
+    // the eight k lie in one segment when its length is a multiple of 8 (k is one)
+    const bool one = p.kseg % 8 == 0 && k + 7 < khi;
+    const int64_t k8 = one ? seg_off(k, p.kseg, seg) : 0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int64_t ko = seg_off(min(k + e, khi - 1), p.kseg, seg);
+      const int64_t ko = one ? k8 + e : seg_off(min(k + e, khi - 1), p.kseg, seg);
       const float x = km ? P[o * ld + ko] : P[ko * ld + o];
       v[g][e] = k + e < khi ? x : 0.0f;
+    }
+  }
+  // all groups as fp32 numbers (fp32_at)
+  __device__ __forceinline__ void store_fp32(char* buf, int tid) const {
+#pragma unroll
+    for (int g = 0; g < 6; ++g) {
+      const int row = g < 4 ? outer_a<AK>(g, tid) : BM + col_row(outer_b<BKM>(g - 4, tid));
+      const int c = 2 * (g < 4 ? chunk_a<AK>(g, tid) : chunk_b<BKM>(g - 4, tid));
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        *reinterpret_cast<f32x4*>(buf + fp32_at(row, c + t)) =
+            f32x4{v[g][4 * t], v[g][4 * t + 1], v[g][4 * t + 2], v[g][4 * t + 3]};
     }
   }
   __device__ __forceinline__ void put(int g, char* buf, int part, const uint32_t (&w)[4]) const {
@@ -238,26 +261,26 @@ __device__ __forceinline__ void clear(Acc& acc) {
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 }
 
-// The fp32 number whose parts sit at element e of three fragments.
-__device__ __forceinline__ float whole_value(const bf16x8& h, const bf16x8& m, const bf16x8& l, int e) {
-  const float x = (float)h[e];
-  return fabsf(x) == INFINITY ? x : (x + (float)m[e]) + (float)l[e];
-}
-
-// acc += the slice in buf as fp32 numbers: element e of the four lane groups'
-// chunks are four k of one 16x16x4 instruction.
-__device__ __forceinline__ void wide_slice(const char* buf, const FragAt& f, Acc& acc) {
+// acc += the slice of fp32 numbers in buf: element e of the four lane groups'
+// eight consecutive k are the four k of one 16x16x4 instruction.
+__device__ __forceinline__ void fp32_slice(const char* buf, int wm, int wn, int lane, Acc& acc) {
+  const int r = lane & 15, c = 2 * (lane >> 4);
+  auto eight = [&](int row, f32x4 (&v)[2]) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const bf16x8 bh = frag_b(buf, f, j, 0), bm = frag_b(buf, f, j, 1), bl = frag_b(buf, f, j, 2);
+    for (int t = 0; t < 2; ++t) v[t] = *reinterpret_cast<const f32x4*>(buf + fp32_at(row, c + t));
+  };
+  f32x4 b[4][2];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const bf16x8 ah = frag_a(buf, f, i, 0), am = frag_a(buf, f, i, 1), al = frag_a(buf, f, i, 2);
+  for (int j = 0; j < 4; ++j) eight(BM + col_row(wn * 64 + 4 * r + j), b[j]);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    f32x4 a[2];
+    eight(wm * 128 + i * 16 + r, a);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(whole_value(ah, am, al, e), whole_value(bh, bm, bl, e),
-                                                         acc[i][j], 0, 0, 0);
-    }
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e >> 2][e & 3], b[j][e >> 2][e & 3], acc[i][j], 0, 0, 0);
   }
 }
 
@@ -478,20 +501,34 @@ __global__ __launch_bounds__(256, 1) void k_gemm_split(GemmF32 p, uint32_t gx, u
           for (int j = 0; j < 4; ++j) acc[i][j] += lo[i][j];
       }
       lds_barrier();
-      sg.move((n & 1) ? 0u - BUF : 0u);  // back to the first buffer
     }
     int64_t k = klo + (int64_t)n * BK;
     if (__builtin_amdgcn_readfirstlane(sm.wide) != 0) {
       clear(acc);
       k = klo;
     }
-    for (; k < khi; k += BK) {
+    auto fp32_part = [&](int64_t ke, Acc& c) {
+      for (; k < ke; k += BK) {
 #pragma unroll
-      for (int g = 0; g < 6; ++g) sg.load_checked(g, p, A, B, i0, j0, k, khi, tid);
-      sg.store_all(sm.p);
-      lds_barrier();
-      wide_slice(sm.p, f, acc);
-      lds_barrier();
+        for (int g = 0; g < 6; ++g) sg.load_checked(g, p, A, B, i0, j0, k, khi, tid);
+        sg.store_fp32(sm.p, tid);
+        lds_barrier();
+        fp32_slice(sm.p, wm, wn, lane, c);
+        lds_barrier();
+      }
+    };
+    if constexpr (DEEP) {
+      while (k < khi) {
+        Acc loc;
+        clear(loc);
+        fp32_part(min(khi, k + FP32_CHUNK * BK), loc);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[i][j] += loc[i][j];
+      }
+    } else {
+      fp32_part(khi, acc);
     }
   }
   // lane c of a row of 16 holds columns 4 c .. 4 c + 3 of the wave's half

@@ -62,30 +62,49 @@ def test_triangular_products_against_fp64(m, n, batch):
     f.close()
 
 
-def test_extreme_values():
-    """Infinities, NaNs, values that round to a bf16 infinity, tiny values:
-    as in an fp32 product with dense operands."""
-    m, n, batch = 128, 132, 256
-    f, A, B = _handle(m, n, batch)
-    X = torch.randn(batch, m, n, generator=torch.Generator().manual_seed(5))
-    X[3, 5, 7] = math.inf
-    X[4, 6, 8] = -math.inf
-    X[5, 7, 9] = math.nan
-    X[6] *= 1e-36
-    X[7] = 0.0
-    X[7, 11, 12] = float(np.finfo(np.float32).max)
-    Y = f.kron_apply(X.cuda()).cpu()
-    ok = torch.ones(batch, dtype=torch.bool)
-    ok[3:6] = False
-    assert torch.isfinite(Y[ok][[0, 1, 2, 3, 5]]).all()
-    assert not torch.isfinite(Y[3:6]).all(dim=2).any()   # every entry's sum meets the non-finite value
-    assert torch.isnan(Y[5]).all()
-    ref = B @ X[6].double() @ A
-    # entries below 2^-126 * 2^16 lose low parts, which sit under fp32's smallest numbers
-    assert float((Y[6].double() - ref).norm() / ref.norm()) <= 1e-3
-    r7 = B @ X[7].double() @ A
-    fin = r7.abs() < 3e38
-    t = B[:, 11].abs().max() * float(np.finfo(np.float32).max) < 3.4e38
-    if t:
-        assert ((Y[7].double() - r7).abs()[fin] <= 1e-6 * r7.abs().max()).all()
+def _dense(d, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    Q = torch.randn(d, d, generator=g, device="cuda", dtype=torch.float64)
+    return (Q @ Q.T / d + torch.eye(d, device="cuda", dtype=torch.float64)).float()
+
+
+# 1536 x 2048: 192 tiles of one matrix
+WIDE_M, WIDE_N = 1536, 2048
+
+
+def _wide_handle(A, B):
+    return ffe.FlipFlop(torch.zeros(1, B.shape[0], A.shape[0], device="cuda"), A0=A, B0=B)
+
+
+@pytest.mark.parametrize("value", [float(np.finfo(np.float32).max), 3.395e38, -3.3895e38])
+def test_entries_near_the_largest_float(value):
+    """Finite as long as the sums are: what an fp32 product gives."""
+    A, B = _dense(WIDE_N, 1) * 0.1, _dense(WIDE_M, 2) * 0.1
+    f = _wide_handle(A, B)
+    X = torch.zeros(1, WIDE_M, WIDE_N, device="cuda")
+    X[0, 11, 12] = value
+    Y = f.kron_apply(X).double()
+    ref = B.double() @ X.double() @ A.double()
+    # one product per sum and two roundings; the second product (of ordinary
+    # numbers) drops parts of up to 2^-22
+    assert bool(torch.isfinite(Y).all())
+    assert float(((Y - ref).abs() / ref.abs()).max()) <= 6 * U32
+    f.close()
+
+
+def test_infinities_and_nans():
+    A, B = _dense(WIDE_N, 1), _dense(WIDE_M, 2)
+    f = _wide_handle(A, B)
+    X = torch.randn(4, WIDE_M, WIDE_N, generator=torch.Generator().manual_seed(5)).cuda()
+    want = f.kron_apply(X[3:].contiguous())
+    X[0, 5, 7] = math.inf
+    X[1, 6, 8] = -math.inf
+    X[2, 7, 9] = math.nan
+    Y = f.kron_apply(X)
+    # column 7 of B X is infinite with the signs of B's column 5, so row i of
+    # the result is infinite with the sign of B[i, 5] A[7, j]
+    assert torch.equal(Y[0], (B[:, 5, None] * A[7]).sign() * math.inf)
+    assert torch.equal(Y[1], (B[:, 6, None] * A[8]).sign() * -math.inf)
+    assert torch.isnan(Y[2]).all()
+    assert torch.equal(Y[3], want[0])
     f.close()
