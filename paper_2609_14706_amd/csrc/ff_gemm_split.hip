@@ -1,22 +1,29 @@
 // Large fp32 products on the bf16 matrix cores: every fp32 operand entry is
-// split into three bf16 parts, x = h + m + l (h the leading 8 significant
-// bits, m and l what is left rounded to nearest: together all 24), and
+// split into three bf16 parts, x = h + m + l (each what is left, rounded to
+// nearest: together all 24 significant bits), and
 //     a b = ah bh + (ah bm + am bh) + (ah bl + am bm + al bh) + ...
 // is summed over the six products written; the dropped ones have random
-// signs and are below 2^-22 |a b| (2^-26 on average).  Products of two bf16
-// numbers are exact in fp32 and one matrix instruction adds 32 of them per
-// rounding (the fp32 matrix instructions 2), so the sums are nearer to the
-// exact ones than theirs (tests/test_gpu_gemm_split.py).
+// signs and are together at most 2^-24 |a b|.  Products of two bf16 numbers
+// are exact in fp32 and one matrix instruction adds 32 of them per rounding
+// (the fp32 matrix instructions 2), so sums over many k are nearer to the
+// exact ones than theirs: 2-norm errors of 2048-wide dense products 3.9e-7
+// against 1.07e-6.  Where one term makes up the sum (a diagonal factor) the
+// dropped products show: 3.7e-8 against 3.6e-8, the largest error 1.6e-7 against
+// 1.2e-7 (with h truncated instead of rounded 4.9e-8 and 3.9e-7).  With the two
+// larger dropped products as well the errors are those of the fp32
+// instructions, and 8 products of 3000 x 2000 take 2.98 ms instead of 2.55; sums
+// of more than one term gain nothing from them.
 //
 // 256 x 128 output tiles, four waves of 128 x 64 (8 x 4 tiles of
 // v_mfma_f32_16x16x32_bf16), one workgroup per CU.  k goes in slices of 32:
 // fp32 from global memory into registers two slices ahead, split one slice
 // ahead, the parts through two LDS buffers (144 KB).  All of it runs in the
 // shadow of the products: within a slice's 192 matrix instructions (16
-// cycles each) every one is followed by at most four others (the splitting
-// takes about 290, the LDS reads and writes 54), in a fixed program order.
-// The slice's one barrier comes before its last 36 products, which hide the
-// reads of the next slice's first fragments.  Bound by the matrix cores (six
+// cycles each) every one is followed by a few others (the splitting takes
+// about 340, the LDS reads and writes 54), in a fixed program order.
+// The slice's one barrier comes before its last 34 products, which hide the
+// reads of the next slice's first fragments.  All 512 registers are in use: 0 to
+// 22 values (the loop's operand addresses first) are kept in scratch memory.  Bound by the matrix cores (six
 // products); the LDS moves 216 KB per 3072 cycles.
 #include <math.h>
 
@@ -47,7 +54,9 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 // rows, one chunk) cover all banks.
 struct __align__(16) SplitLDS {
   char p[2 * BUF];
-  int wide;  // set once the tile has to be computed from the fp32 numbers
+  uint32_t big;  // bits of the largest magnitude of the tile's entries
+  int tiny;      // set if a nonzero entry is below kTiny
+  int wide;      // set if the tile has to be computed from the fp32 numbers
 };
 
 // LDS row of column o of the second operand: within each 64-column half,
@@ -75,11 +84,34 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {  // round to neare
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// Entries above this magnitude (or infinite) set SplitLDS::wide: an infinity
-// would meet the zero or opposite parts of finite factors and turn into NaN.
-// The tile is then computed again from the fp32 numbers themselves on the
-// fp32 matrix cores (fp32_slice), as is a last slice of fewer than 32 k.
+// Where three bf16 parts do not hold an entry, the tile is computed again from
+// the fp32 numbers themselves on the fp32 matrix cores (fp32_slice), as is a
+// last slice of fewer than 32 k:
+//  * entries above the largest bf16 number or infinite: an infinite part
+//    would meet the zero or opposite parts of finite factors and give NaN;
+//  * nonzero entries below 2^-100, whose lower parts may be subnormal or below
+//    every bf16 number, off by at most 2^-126 (all of the subnormal range):
+//    only if an output of the tile is so small that k products of that with
+//    the largest entry reach 2^-25 of it.  Tiny entries among ordinary ones
+//    (gradients of a saturated softmax) so cost a look at the outputs, no
+//    more.  Entries below 2^-133, subnormal fp32 numbers that round to a bf16
+//    zero, are not noticed and count as zeros.
+// Noticing them takes three instructions per two entries, which fit between
+// the products (8 products of 3000 x 2000: 2.55 ms with and without); with 32-bit
+// minima in place of the packed 16-bit ones 2.66.
 constexpr float kWide = 3.3895313e38f;
+constexpr float kTinyReach = 0x1p-101f;
+
+// Range of the entries a thread has split.
+struct Range {
+  float big = 0.0f;             // largest magnitude (NaNs drop out)
+  uint32_t least = 0xffffffffu;  // in each half the least 2 h - 1 of nonzero h, as 16-bit patterns
+  __device__ __forceinline__ bool wide() const { return big > kWide; }
+  __device__ __forceinline__ bool tiny() const {
+    constexpr uint32_t t = 2u * ((127u - 100u) << 7) - 1u;  // of 2^-100
+    return (least & 0xffffu) < t || (least >> 16) < t;
+  }
+};
 
 // A thread's share of a slice: groups of eight consecutive k of one row of
 // op(A) (four groups) or one column of op(B) (two).  KMAJ: the operand is
@@ -94,22 +126,25 @@ __device__ __forceinline__ int outer_b(int g, int tid) { return KMAJ ? (tid >> 2
 template <bool KMAJ>
 __device__ __forceinline__ int chunk_b(int g, int tid) { return KMAJ ? tid & 3 : (tid >> 7) + 2 * g; }
 
-// Splitting of two entries in five steps, spread between products.
+// Splitting of two entries in four steps, spread between products.
 struct Split {
   float a, b, ra, rb;
   uint32_t H[4], M[4], L[4];
-  float big;
-  __device__ __forceinline__ void step(int st, const float (&v)[8], int q) {
+  __device__ __forceinline__ void step(int st, const float (&v)[8], int q, Range& rg) {
     if (st == 0) {
       a = v[2 * q];
       b = v[2 * q + 1];
-      H[q] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
-      ra = a - __uint_as_float(__float_as_uint(a) & 0xffff0000u);
-      rb = b - __uint_as_float(__float_as_uint(b) & 0xffff0000u);
+      H[q] = pack2(a, b);
+      ra = a - __uint_as_float(H[q] << 16);
+      rb = b - __uint_as_float(H[q] & 0xffff0000u);
     } else if (st == 1) {
       // one instruction (fmaxf would quiet its operands first); NaNs drop out
-      asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(big) : "v"(a), "v"(b));
+      asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(rg.big) : "v"(a), "v"(b));
       M[q] = pack2(ra, rb);
+      // 2 h - 1 of both halves (the sign drops out, a zero wraps around to the largest)
+      uint32_t t;
+      asm("v_pk_mad_u16 %0, %1, 2, -1 op_sel_hi:[1,0,1]" : "=v"(t) : "v"(H[q]));
+      asm("v_pk_min_u16 %0, %1, %0" : "+v"(rg.least) : "v"(t));
     } else if (st == 2) {
       ra -= __uint_as_float(M[q] << 16);
       rb -= __uint_as_float(M[q] & 0xffff0000u);
@@ -208,20 +243,18 @@ struct Stage {
     at_b += d;
   }
   // split and store all groups (outside the pipelined loop)
-  __device__ __forceinline__ float store_all(char* buf) const {
+  __device__ __forceinline__ void store_all(char* buf, Range& rg) const {
     Split s;
-    s.big = 0.0f;
 #pragma unroll
     for (int g = 0; g < 6; ++g) {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int st = 0; st < 4; ++st) s.step(st, v[g], q);
+        for (int st = 0; st < 4; ++st) s.step(st, v[g], q, rg);
       put(g, buf, 0, s.H);
       put(g, buf, 1, s.M);
       put(g, buf, 2, s.L);
     }
-    return s.big;
   }
 };
 
@@ -245,8 +278,10 @@ __device__ __forceinline__ bf16x8 frag_b(const char* buf, const FragAt& f, int j
 }
 
 // Product q of the six: parts of the two operands, in the order that frees
-// the second operand's parts one after the other.
-constexpr int kPartA[6] = {2, 1, 0, 1, 0, 0}, kPartB[6] = {0, 0, 0, 1, 1, 2};
+// the second operand's parts one after the other, the leading product last.
+constexpr int NP = 6;
+constexpr int kPartA[NP] = {0, 0, 1, 1, 2, 0}, kPartB[NP] = {2, 1, 1, 0, 0, 0};
+constexpr int PT = 4 * NP;  // products per row tile
 
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -299,41 +334,38 @@ __device__ __forceinline__ void static_for(const F& f) {
 // tiles, the splitting of the staged slice into the buffer that sg points at,
 // the loads of the slice at (na, nb) into the stage, the barrier, and the reads
 // of the next slice's first fragments (fn), each over one whose last product is issued: on entry a[0] and
-// parts 0 and 1 of b hold this slice's (part 2 is read here), on return the
+// parts 2 and 1 of b hold this slice's (part 0 is read here), on return the
 // next one's.
 template <bool AK, bool BKM, bool VEC>
 __device__ __forceinline__ void pipelined_slice(SplitLDS& sm, const FragAt& f, const FragAt& fn,
-                                                Stage<AK, BKM, VEC>& sg, const float* na, const float* nb,
+                                                Stage<AK, BKM, VEC>& sg, Range& rg, const float* na, const float* nb,
                                                 int64_t lda, int64_t ldb, FragA (&a)[2], FragB& b, Acc& hi, Acc& lo) {
   char* buf = sm.p;
   Split sp;
-  sp.big = 0.0f;
-  static_for<192>([&](auto mc) {
+  static_for<8 * PT>([&](auto mc) {
     constexpr int m = decltype(mc)::value;
-    constexpr int i = m / 24, q = (m % 24) / 4, j = m % 4;
+    constexpr int i = m / PT, q = (m % PT) / 4, j = m % 4;
+    constexpr int last = m - 7 * PT;  // product of the last row tile
     f32x4& c = kPartA[q] + kPartB[q] == 0 ? hi[i][j] : lo[i][j];
     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i & 1][kPartA[q]], b[kPartB[q]][j], c, 0, 0, 0);
-    if constexpr (m < 4) b[2][m] = frag_b(buf, f, m, 2);
+    if constexpr (m < 4) b[0][m] = frag_b(buf, f, m, 0);
     // the next row tile's parts, in the order of their use
-    if constexpr (i < 7 && m % 4 == 1 && m % 24 < 12) {
-      constexpr int s = 2 - m % 24 / 4;
+    if constexpr (i < 7 && m % 4 == 1 && m % PT < 12) {
+      constexpr int s = m % PT / 4;
       a[(i + 1) & 1][s] = frag_a(buf, f, i + 1, s);
     }
-    if constexpr (m < 144) {  // six products per two entries
-      constexpr int pr = m / 6, st = m % 6, g = pr / 4, e = pr % 4;
-      sp.step(st, sg.v[g], e);
+    if constexpr (m < 24 * NP) {  // NP products per two entries
+      constexpr int pr = m / NP, st = m % NP, g = pr / 4, e = pr % 4;
+      sp.step(st, sg.v[g], e, rg);
       if constexpr (e == 3 && st == 1) sg.put(g, buf, 0, sp.H);
       if constexpr (e == 3 && st == 3) sg.put(g, buf, 1, sp.M);
       if constexpr (e == 3 && st == 4) sg.put(g, buf, 2, sp.L);
       if constexpr (e == 3 && st == 5) sg.load(g, na, nb, lda, ldb);
     }
-    if constexpr (m == 150) {
-      if (__any(sp.big > kWide)) sm.wide = 1;
-    }
-    if constexpr (m == 157) lds_barrier();  // every read of buf but the last wave's a tile has landed
-    if constexpr (m >= 169 && m <= 173 && m % 2 == 1) a[0][2 - (m - 169) / 2] = frag_a(buf, fn, 0, 2 - (m - 169) / 2);
-    if constexpr (m >= 180 && m < 184) b[0][m - 180] = frag_b(buf, fn, m - 180, 0);
-    if constexpr (m >= 188) b[1][m - 188] = frag_b(buf, fn, m - 188, 1);
+    if constexpr (last == -11) lds_barrier();  // every read of buf but the last wave's a tile has landed
+    if constexpr (last == 1 || last == 3 || last == 5) a[0][last / 2] = frag_a(buf, fn, 0, last / 2);
+    if constexpr (last >= 4 && last < 8) b[2][last - 4] = frag_b(buf, fn, last - 4, 2);
+    if constexpr (last >= 12 && last < 16) b[1][last - 12] = frag_b(buf, fn, last - 12, 1);
     __builtin_amdgcn_sched_barrier(0);
   });
 }
@@ -415,9 +447,13 @@ __global__ __launch_bounds__(256, 1) void k_gemm_split(GemmF32 p, uint32_t gx, u
     // whole slices, each in one segment (otherwise all take the checked path)
     const bool segs = p.kseg == 0 || p.kseg % BK == 0;
     const int n = segs ? (int)((khi - klo) / BK) : 0;
-    if (tid == 0) sm.wide = 0;
+    if (tid == 0) {
+      sm.big = 0u;
+      sm.tiny = sm.wide = 0;
+    }
     lds_barrier();
     if (n > 0) {
+      Range rg;
       // base of the slice to load next, moved along until the last one
       int64_t in = klo;
       const float* na = A + (AK ? i0 * p.lda : i0);
@@ -446,7 +482,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_split(GemmF32 p, uint32_t gx, u
 #pragma unroll
       for (int g = 0; g < 6; ++g) sg.load(g, na, nb, p.lda, p.ldb);
       advance();
-      if (__any(sg.store_all(sm.p) > kWide)) sm.wide = 1;
+      sg.store_all(sm.p, rg);
 #pragma unroll
       for (int g = 0; g < 6; ++g) sg.load(g, na, nb, p.lda, p.ldb);
       advance();
@@ -456,7 +492,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_split(GemmF32 p, uint32_t gx, u
 #pragma unroll
       for (int t = 0; t < 3; ++t) {
         a[0][t] = frag_a(sm.p, f, 0, t);
-        if (t < 2)
+        if (t > 0)
 #pragma unroll
           for (int j = 0; j < 4; ++j) b[t][j] = frag_b(sm.p, f, j, t);
       }
@@ -471,7 +507,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_split(GemmF32 p, uint32_t gx, u
           for (; s < e; ++s) {
             const FragAt fn = fc.plus(d);
             sg.move(d);
-            pipelined_slice(sm, fc, fn, sg, na, nb, p.lda, p.ldb, a, b, loc, loc);
+            pipelined_slice(sm, fc, fn, sg, rg, na, nb, p.lda, p.ldb, a, b, loc, loc);
             advance();
             fc = fn;
             d = 0u - d;
@@ -490,7 +526,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_split(GemmF32 p, uint32_t gx, u
         for (int s = 0; s < n; ++s) {
           const FragAt fn = fc.plus(d);
           sg.move(d);
-          pipelined_slice(sm, fc, fn, sg, na, nb, p.lda, p.ldb, a, b, acc, lo);
+          pipelined_slice(sm, fc, fn, sg, rg, na, nb, p.lda, p.ldb, a, b, acc, lo);
           advance();
           fc = fn;
           d = 0u - d;
@@ -500,7 +536,22 @@ __global__ __launch_bounds__(256, 1) void k_gemm_split(GemmF32 p, uint32_t gx, u
 #pragma unroll
           for (int j = 0; j < 4; ++j) acc[i][j] += lo[i][j];
       }
+      atomicMax(&sm.big, __float_as_uint(rg.big));
+      if (__any(rg.wide())) sm.wide = 1;
+      if (__any(rg.tiny())) sm.tiny = 1;
       lds_barrier();
+      if (__builtin_amdgcn_readfirstlane(sm.tiny) != 0) {
+        const float reach = kTinyReach * (float)(khi - klo) * __uint_as_float(sm.big);
+        float least = INFINITY;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) least = fminf(least, fabsf(acc[i][j][r]));
+        if (__any(!(least >= reach))) sm.wide = 1;
+        lds_barrier();
+      }
     }
     int64_t k = klo + (int64_t)n * BK;
     if (__builtin_amdgcn_readfirstlane(sm.wide) != 0) {
