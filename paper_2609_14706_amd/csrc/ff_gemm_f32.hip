@@ -10,6 +10,8 @@
 // k can be split over the grid into partial outputs.  When every operand is
 // 16-byte aligned with leading dimensions divisible by 4, global loads are
 // 16-byte vectors (edge vectors fall back to element loads).
+#include <algorithm>
+
 #include "ff_common.hpp"
 #include "ff_kernels.hpp"
 
@@ -273,8 +275,46 @@ hipError_t launch_tiles(const GemmF32& p, int batch, bool vec, bool deep, hipStr
   return hipGetLastError();
 }
 
+// Which route is faster, from the work that the busiest CU gets in each, in
+// units of one k of a 64 x 64 tile (25 ns; 35 where its loads are checked):
+//  * 64 x 64 tiles: one k each, rounds of 256 tiles, triangular ranges evened
+//    out over the rounds;
+//  * 256 x 128 tiles of three-part products: three units a k and about 128 k
+//    to begin and end, rounds of 256 tiles, the first of which has the longest
+//    range.
+// Partly empty tiles and rounds count in full on both sides, so many products
+// smaller than a large tile stay with the small ones.  Measured, us, 64 x 64
+// tiles against 256 x 128: dense 1408 square 71 / 112, 1500 square 175 / 132,
+// 2048 square 194 / 159, 2000 x 3000 618 / 238; eight of 1024 square 196 / 92; 2048
+// of 64 square 24 / 114, 2048 of 16 square 22 / 95, 1024 of 128 square 65 / 84;
+// triangular 2304 square 150 / 174, 2600 square 241 / 205; 65536 whitened rows of
+// 64 14 / 21, of 192 57 / 58, of 256 86 / 67, of 512 273 / 198; symmetric from 65536 k in
+// parts, 192 wide 58 / 85, 256 wide 143 / 87, 1024 wide 1869 / 675.
+bool gemm_takes_split(const GemmF32& p, int batch, bool vec) {
+  const bool lower = (p.flags & kCLower) != 0;
+  if (p.tile == 64 || (lower && p.M != p.N) || p.lda > kSplitMaxLd || p.ldb > kSplitMaxLd) return false;
+  if (p.M <= 128) return false;  // half of every large tile or more is empty
+  auto parts = [](int64_t x, int64_t t) { return (x + t - 1) / t; };
+  const int64_t z = p.ksplit > 1 ? p.ksplit : batch;
+  const int64_t m64 = parts(p.M, 64), m256 = parts(p.M, 256), n128 = parts(p.N, 128);
+  int64_t small = m64 * parts(p.N, 64), large = m256 * n128;
+  if (lower) {
+    small = m64 * (m64 + 1) / 2;
+    large = 0;
+    for (int64_t b = 1; b <= m256; ++b) large += std::min<int64_t>(2 * b, n128);
+  }
+  const double k = p.ksplit > 1 ? (double)parts(p.K, p.ksplit) : (double)p.K;
+  const bool row = (p.flags & (kKHiRow | kKLoRow)) != 0, col = (p.flags & (kKHiCol | kKLoCol)) != 0;
+  // mean ranges of the tiles
+  const double k_small = row || col ? std::min(k, (k + 64) / 2) : k;
+  const double k_large = row ? std::min(k, (k + 256) / 2) : col ? std::min(k, (k + 128) / 2) : k;
+  const double r_small = (double)parts(small * z, 256), r_large = (double)parts(large * z, 256);
+  const bool whole = vec && p.ksplit <= 1 && p.M % 64 == 0 && p.N % 64 == 0 && p.K % 64 == 0;
+  return r_small * k_small * (whole ? 1.0 : 1.4) > 3.0 * (std::max(k, r_large * k_large) + 128.0 * r_large);
+}
+
 hipError_t launch_gemm_f32(const GemmF32& p, int batch, hipStream_t s) {
-  if (p.M < 0 || p.N < 0 || p.K < 0 || batch < 1 || p.kseg < 1) return hipErrorInvalidValue;
+  if (p.M < 0 || p.N < 0 || p.K < 0 || batch < 1) return hipErrorInvalidValue;
   if (p.ksplit > 1 && batch != 1) return hipErrorInvalidValue;
   if (p.M == 0 || p.N == 0) return hipSuccess;
   const bool segmented = p.kseg < p.K;
@@ -286,20 +326,7 @@ hipError_t launch_gemm_f32(const GemmF32& p, int batch, hipStream_t s) {
                    (!segmented || (p.kseg % 4 == 0 && p.segA % 4 == 0 && p.segB % 4 == 0));
   GemmF32 q = p;
   if (!segmented) q.kseg = 0;  // plain k axis: the kernels skip the segment arithmetic
-  // The three-part products win once they fill enough of the GPU, counted in
-  // tiles of 128 x 128 (half a 256 x 128 tile each); below, 64 x 64 tiles fill
-  // it better.  Four pairs of dense products (B X A): 196 tiles (1792 x 1792)
-  // 1.19 ms against 1.38, 169 (1600 x 1600) 1.07 against 1.01.  With a triangular
-  // operand (and more than one tile along its index) the longest tiles finish
-  // alone, the more so the fewer there are: four inverse applications with
-  // 441 tiles (2600 x 2600) 5.1 ms against 6.3, 324 (2304 x 2304) 4.3 against 3.9.
-  const int64_t big_tiles = ((p.M + 127) / 128) * ((p.N + 127) / 128) *
-                            (p.ksplit > 1 ? p.ksplit : batch);
-  const bool square = !(p.flags & kCLower) || p.M == p.N;
-  const bool tri = ((p.flags & (kKHiRow | kKLoRow)) && p.M > 128) ||
-                   ((p.flags & (kKHiCol | kKLoCol)) && p.N > 128);
-  if (p.tile != 64 && big_tiles >= (tri ? kSplitMinTri : kSplitMinDense) && square && p.lda <= kSplitMaxLd && p.ldb <= kSplitMaxLd)
-    return launch_gemm_split(q, batch, vec, deep, s);
+  if (gemm_takes_split(p, batch, vec)) return launch_gemm_split(q, batch, vec, deep, s);
   return launch_tiles(q, batch, vec, deep, s);
 }
 

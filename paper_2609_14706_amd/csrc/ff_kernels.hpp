@@ -78,7 +78,7 @@ struct GemmF32 {
   int tile;            // 0: chosen by size; 64: 64 x 64 tiles
 };
 // C = alpha * op(A) op(B) + beta * C: on the fp32 matrix cores in 64 x 64
-// tiles, or, when it fills the GPU with larger ones, with launch_gemm_split.
+// tiles, or with launch_gemm_split where that is faster (gemm_takes_split).
 hipError_t launch_gemm_f32(const GemmF32& p, int batch, hipStream_t s);
 // The same on the bf16 matrix cores, every fp32 entry split into three bf16
 // parts; 256 x 128 tiles (ff_gemm_split.hip).  kseg = 0: plain k axis.  vec:
@@ -86,9 +86,10 @@ hipError_t launch_gemm_f32(const GemmF32& p, int batch, hipStream_t s);
 // divisible by 4.  deep: k per workgroup beyond 16384.  With kCLower M = N;
 // lda, ldb <= kSplitMaxLd (32-bit offsets within a tile's slice).
 constexpr int64_t kSplitMaxLd = 1 << 23;
-// Tiles of 128 x 128 from which launch_gemm_f32 takes it (reasons there).
-constexpr int64_t kSplitMinDense = 192, kSplitMinTri = 400;
 hipError_t launch_gemm_split(const GemmF32& p, int batch, bool vec, bool deep, hipStream_t s);
+// Whether launch_gemm_f32 takes it (from the sizes, flags, ksplit, tile, lda
+// and ldb of p alone).
+bool gemm_takes_split(const GemmF32& p, int batch, bool vec);
 
 // F (dim x dim) = scale * sum_z P[z] with P[z] row-major dim_p x dim_p, lower
 // triangle read, mirrored.

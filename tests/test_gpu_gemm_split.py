@@ -1,7 +1,8 @@
 """The large fp32 products (three bf16 parts per entry, csrc/ff_gemm_split.hip)
-through ff_kron_apply, which takes them once a launch has 192 tiles of
-128 x 128 (400 with a triangular operand of more than one tile): at tile edges
-and remainders, both operand layouts, triangular operands, against fp64."""
+through ff_kron_apply, which takes them where they are the faster route
+(tests/test_gemm_route_cpu.py), and by themselves: at tile edges and
+remainders, every operand layout, triangular operands, segments, partial sums,
+small, large and infinite entries, against fp64."""
 import ctypes
 import math
 
@@ -31,7 +32,7 @@ def _handle(m, n, batch):
 # rows, columns and k: below, at and above the 128 tile and the 32-wide k
 # slice, odd (scalar loads) and multiples of four (16-byte loads)
 SHAPES = [(255, 127, 260), (256, 128, 256), (36, 33, 300), (1, 130, 256), (257, 31, 130), (300, 1, 260),
-          (264, 200, 70), (520, 132, 80)]
+          (264, 200, 70), (520, 132, 80), (520, 516, 40), (2049, 1537, 1)]
 
 
 @pytest.mark.parametrize("m,n,batch", SHAPES)
@@ -52,7 +53,23 @@ def test_products_against_fp64(m, n, batch):
     f.close()
 
 
-@pytest.mark.parametrize("m,n,batch", [(127, 129, 260), (256, 260, 70), (36, 33, 300)])
+@pytest.mark.parametrize("m,n", [(1024, 1024), (520, 516)])
+def test_one_matrix_alone_and_in_a_batch(m, n):
+    """The batch may change the route and with it the last bits of a matrix's
+    result, no more: both are as near to the exact product as fp32 sums are."""
+    f, A, B = _handle(m, n, 40)
+    X = torch.randn(40, m, n, generator=torch.Generator().manual_seed(3))
+    together, alone = f.kron_apply(X.cuda())[7], f.kron_apply(X[7:8].cuda())[0]
+    ref = B @ X[7].double() @ A
+    for Y in (together, alone):
+        # two products of K / 2 roundings of either sign
+        assert float((Y.cpu().double() - ref).norm() / ref.norm()) <= U32 * math.sqrt((m + n) / 2)
+    # the same call gives the same bits
+    assert torch.equal(alone, f.kron_apply(X[7:8].cuda())[0])
+    f.close()
+
+
+@pytest.mark.parametrize("m,n,batch", [(127, 129, 260), (256, 260, 70), (36, 33, 300), (520, 516, 40)])
 def test_triangular_products_against_fp64(m, n, batch):
     f, A, B = _handle(m, n, batch)
     X = torch.randn(batch, m, n, generator=torch.Generator().manual_seed(4))
