@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "ff.h"
+#include "ff_forkjoin.hpp"
 #include "ff_kernels.hpp"
 
 using namespace ff;
@@ -411,6 +412,17 @@ void give_side_streams(Side& s, int device) {
   s.istream = nullptr;
 }
 
+// `to` waits for everything enqueued on `from` so far.  If the event cannot
+// be used, the host waits instead: on return the order holds either way,
+// unless the device itself failed.
+ff_status stream_waits(hipStream_t to, hipStream_t from, hipEvent_t ev) {
+  hipError_t e = hipEventRecord(ev, from);
+  if (e == hipSuccess) e = hipStreamWaitEvent(to, ev, 0);
+  if (e == hipSuccess) return FF_OK;
+  (void)hipStreamSynchronize(from);
+  return fail(FF_ERR_HIP, std::string("ordering two streams: ") + hipGetErrorString(e));
+}
+
 constexpr int64_t kTwoLevel = 6144;  // wider factors go in outer panels (see chol_blocked)
 
 // Off-diagonal blocks of L^-1 for the node [o, o + sz) of the leaf tree, on
@@ -539,18 +551,13 @@ ff_status chol_blocked(ff_handle_s* h, Side& s, int iteration) {
   const int64_t outer = d > kTwoLevel ? kOuter : nb * kLeaf;
   hipStream_t ms = h->stream;
   hipStream_t is = two ? s.istream : ms;
-  // the inverse stream starts after the work already on the main stream
-  if (two) {
-    FF_HIP(hipEventRecord(s.ev_leaf, ms));
-    FF_HIP(hipStreamWaitEvent(is, s.ev_leaf, 0));
-  }
   int64_t handed = 0;  // leaves whose inverse products are enqueued
   // Leaves [handed, upto] are done, and the panel below leaf upto too when
   // panel_done (all earlier panels are).
   auto hand_over = [&](int64_t upto, bool panel_done) -> ff_status {
     if (two) {
-      FF_HIP(hipEventRecord(s.ev_leaf, ms));
-      FF_HIP(hipStreamWaitEvent(is, s.ev_leaf, 0));
+      const ff_status r1 = stream_waits(is, ms, s.ev_leaf);
+      if (r1 != FF_OK) return r1;
     }
     for (int64_t j = handed; j <= upto; ++j) {
       ff_status r2 = inverse_p2_ending(h, s, 0, d, j, is);
@@ -563,42 +570,44 @@ ff_status chol_blocked(ff_handle_s* h, Side& s, int iteration) {
     handed = upto + 1;
     return FF_OK;
   };
-  for (int64_t p = 0; p < d; p += outer) {
-    const int64_t pe = std::min(p + outer, d);
-    // the outer panel's first diagonal block has every earlier update
-    FF_HIP(launch_chol_step(s.L, s.Li, d, ld, p, -1, 0, s.slots, iteration, s.code, h->st, ms));
-    for (int64_t o = p; o + kLeaf < pe || (o + kLeaf < d && o + kLeaf == pe); o += kLeaf) {
-      const int64_t k = o / kLeaf, rest = d - o - kLeaf;
-      // the panel L_ik = A_ik Li_kk^T, in place
-      FF_HIP(launch_panel_solve(s.L + (o + kLeaf) * ld + o, s.Li + o * ld + o, ld, rest, h->st, ms));
-      // every kInvEvery panels, and every second one among the last
-      // kInvEvery and the one before the last leaf (the last steps leave most
-      // CUs idle for the tree's products)
-      const bool tail = k + 1 + kInvEvery >= nb && ((k + 1) % 2 == 0 || k + 2 == nb);
-      if (((k + 1) % kInvEvery == 0 || tail) && (rc = hand_over(k, true)) != FF_OK) return rc;
-      if (o + kLeaf == pe) break;  // the last panel of the outer panel
-      // diagonal block k + 1 and the panel's update of the outer panel's columns
-      FF_HIP(launch_chol_step(s.L, s.Li, d, ld, o + kLeaf, o, pe, s.slots, iteration, s.code, h->st, ms));
+  auto enqueue = [&]() -> ff_status {
+    for (int64_t p = 0; p < d; p += outer) {
+      const int64_t pe = std::min(p + outer, d);
+      // the outer panel's first diagonal block has every earlier update
+      FF_HIP(launch_chol_step(s.L, s.Li, d, ld, p, -1, 0, s.slots, iteration, s.code, h->st, ms));
+      for (int64_t o = p; o + kLeaf < pe || (o + kLeaf < d && o + kLeaf == pe); o += kLeaf) {
+        const int64_t k = o / kLeaf, rest = d - o - kLeaf;
+        // the panel L_ik = A_ik Li_kk^T, in place
+        FF_HIP(launch_panel_solve(s.L + (o + kLeaf) * ld + o, s.Li + o * ld + o, ld, rest, h->st, ms));
+        // every kInvEvery panels, and every second one among the last
+        // kInvEvery and the one before the last leaf (the last steps leave most
+        // CUs idle for the tree's products)
+        const bool tail = k + 1 + kInvEvery >= nb && ((k + 1) % 2 == 0 || k + 2 == nb);
+        if (((k + 1) % kInvEvery == 0 || tail) && (rc = hand_over(k, true)) != FF_OK) return rc;
+        if (o + kLeaf == pe) break;  // the last panel of the outer panel
+        // diagonal block k + 1 and the panel's update of the outer panel's columns
+        FF_HIP(launch_chol_step(s.L, s.Li, d, ld, o + kLeaf, o, pe, s.slots, iteration, s.code, h->st, ms));
+      }
+      if (pe < d) {
+        // A_22 -= L_21 L_21^T over the outer panel's columns
+        GemmF32 g{};
+        g.lda = g.ldb = g.ldc = ld;
+        g.kseg = INT64_MAX / 4;
+        g.ksplit = 1;
+        g.st = h->st;
+        g.A = s.L + pe * ld + p; g.B = g.A; g.C = s.L + pe * ld + pe;
+        g.M = d - pe; g.N = d - pe; g.K = pe - p;
+        g.transA = 0; g.transB = 1; g.alpha = -1.f; g.beta = 1.f; g.flags = kCLower;
+        FF_HIP(launch_gemm_f32(g, 1, ms));
+      }
     }
-    if (pe < d) {
-      // A_22 -= L_21 L_21^T over the outer panel's columns
-      GemmF32 g{};
-      g.lda = g.ldb = g.ldc = ld;
-      g.kseg = INT64_MAX / 4;
-      g.ksplit = 1;
-      g.st = h->st;
-      g.A = s.L + pe * ld + p; g.B = g.A; g.C = s.L + pe * ld + pe;
-      g.M = d - pe; g.N = d - pe; g.K = pe - p;
-      g.transA = 0; g.transB = 1; g.alpha = -1.f; g.beta = 1.f; g.flags = kCLower;
-      FF_HIP(launch_gemm_f32(g, 1, ms));
-    }
-  }
-  if ((rc = hand_over(nb - 1, false)) != FF_OK) return rc;
-  if (two) {
-    FF_HIP(hipEventRecord(s.ev_inv, is));
-    FF_HIP(hipStreamWaitEvent(ms, s.ev_inv, 0));
-  }
-  return FF_OK;
+    return hand_over(nb - 1, false);
+  };
+  if (!two) return enqueue();
+  // the inverse stream starts after the work already on the main stream, and
+  // the main stream goes on after it
+  return fork_join([&] { return stream_waits(is, ms, s.ev_leaf); }, enqueue, [] { return FF_OK; },
+                   [&] { return stream_waits(ms, is, s.ev_inv); });
 }
 
 // Automatic split (whiten_split = 0): whiten with the hi + lo bf16 parts of
@@ -669,24 +678,22 @@ ff_status aux_stream(ff_handle_s* h) {
 }
 
 // fA() with the work it enqueues on the handle's stream, fB() on the second
-// one, forked from the handle's stream and joined back into it: A's and B's
-// factorisations are independent and latency bound (a 4096 pair 3.6 ms one
-// after the other, 2.6 side by side).
+// one, forked from the handle's stream and joined back into it (also when
+// either fails): A's and B's factorisations are independent and latency bound
+// (a 4096 pair 3.6 ms one after the other, 2.6 side by side).
 template <class FA, class FB>
 ff_status side_by_side(ff_handle_s* h, const FA& fA, const FB& fB) {
   ff_status rc = aux_stream(h);
   if (rc != FF_OK) return rc;
-  FF_HIP(hipEventRecord(h->fork, h->stream));
-  FF_HIP(hipStreamWaitEvent(h->aux, h->fork, 0));
-  if ((rc = fA()) != FF_OK) return rc;
   const hipStream_t main = h->stream;
-  h->stream = h->aux;
-  rc = fB();
-  h->stream = main;
-  if (rc != FF_OK) return rc;
-  FF_HIP(hipEventRecord(h->join, h->aux));
-  FF_HIP(hipStreamWaitEvent(h->stream, h->join, 0));
-  return FF_OK;
+  return fork_join([&] { return stream_waits(h->aux, main, h->fork); }, fA,
+                   [&] {
+                     h->stream = h->aux;
+                     const ff_status r = fB();
+                     h->stream = main;
+                     return r;
+                   },
+                   [&] { return stream_waits(main, h->aux, h->join); });
 }
 
 // L^-1 of both factors (label -1: not part of an iteration).
