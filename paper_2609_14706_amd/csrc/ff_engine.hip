@@ -702,18 +702,24 @@ ff_status cholinv_both(ff_handle_s* h, const float* Af, const float* Bf) {
                       [&] { return cholinv_from(h, h->B, Bf, -1); });
 }
 
-// After cholinv_both failed: the error for the factor to blame, A if it is
-// not positive definite (both may not be, and the two streams' failures come
-// in any order), with the status cleared.
-ff_status blame_factor(ff_handle_s* h, const float* Af, const char* where) {
+// After side by side factorisations failed: the error for the factor to
+// blame, A if it is not positive definite (both may not be, and the two
+// streams' failures come in any order), with the status cleared.  again_A
+// factorises A once more, by itself.
+template <class AgainA>
+ff_status blame_factor(ff_handle_s* h, const AgainA& again_A, const char* where) {
   ff_status rc = clear_status(h);
-  if (rc != FF_OK || (rc = cholinv_from(h, h->A, Af, -1)) != FF_OK) return rc;
+  if (rc != FF_OK || (rc = again_A()) != FF_OK) return rc;
   int st[4];
   if ((rc = read_status(h, st)) != FF_OK) return rc;
   if ((rc = clear_status(h)) != FF_OK) return rc;
   FF_HIP(hipStreamSynchronize(h->stream));
   return fail(FF_ERR_NOT_SPD, std::string("factor ") + (st[0] != 0 ? "A" : "B") +
                                   " not positive definite in " + where);
+}
+
+ff_status blame_inverse(ff_handle_s* h, const float* Af, const char* where) {
+  return blame_factor(h, [&] { return cholinv_from(h, h->A, Af, -1); }, where);
 }
 
 // Frobenius estimator: the half steps B = (1/(N n)) sum_i G_i A G_i^T and
@@ -1274,16 +1280,19 @@ QuantLayout quant_layout(int64_t m, int64_t n) {
   return q;
 }
 
+// J M J of one side's M factorised in s.L / s.Li.
+ff_status quant_factor(ff_handle_s* h, Side& s, const float* M) {
+  FF_HIP(launch_wk_reverse(M, s.dim, s.L, s.ld, h->st, h->stream));
+  Timed t(h, 3, (double)s.dim * s.dim * s.dim / 3.0);
+  return chol_blocked(h, s, -1);
+}
+
 // Normalised inverse of RevCholesky(M) (padded), its diagonal and the padded
-// scales of one side: J M J is factorised in s.L / s.Li.
+// scales of one side.
 ff_status quant_side(ff_handle_s* h, Side& s, const float* M, int64_t dq, float* Lt, float* diag,
                      double gamma, int given, float* user, float* scale) {
-  FF_HIP(launch_wk_reverse(M, s.dim, s.L, s.ld, h->st, h->stream));
-  {
-    Timed t(h, 3, (double)s.dim * s.dim * s.dim / 3.0);
-    ff_status rc = chol_blocked(h, s, -1);
-    if (rc != FF_OK) return rc;
-  }
+  ff_status rc = quant_factor(h, s, M);
+  if (rc != FF_OK) return rc;
   FF_HIP(launch_wk_normalise(s.Li, s.ld, s.dim, dq, Lt, diag, h->st, h->stream));
   FF_HIP(launch_wk_scales(diag, s.dim, dq, s.slots, s.nslots, gamma, given, user, scale, h->st,
                           h->stream));
@@ -1536,7 +1545,7 @@ ff_status ff_kron_apply(ff_handle h, const float* X, float* Y, int64_t batch, ff
   if ((rc = read_status(h, st)) != FF_OK) return rc;
   if (st[0] != 0) {
     h->A.lw_valid = h->B.lw_valid = false;
-    return blame_factor(h, h->A.F[cur], "ff_kron_apply");
+    return blame_inverse(h, h->A.F[cur], "ff_kron_apply");
   }
   return FF_OK;
 }
@@ -1565,7 +1574,7 @@ ff_status ff_objective(ff_handle h, const float* A, const float* B, double* psi)
     FF_HIP(hipMemcpyAsync(terms, out, sizeof terms, hipMemcpyDeviceToHost, h->stream));
     int st[4];
     if ((rc = read_status(h, st)) != FF_OK) return rc;
-    if (st[0] != 0) return blame_factor(h, Af, "ff_objective");
+    if (st[0] != 0) return blame_inverse(h, Af, "ff_objective");
     const double mn = (double)h->m * (double)h->n;
     *psi = log(terms[0] / ((double)h->N * mn)) + terms[1] / (double)h->n + terms[2] / (double)h->m;
     return FF_OK;
@@ -1593,7 +1602,7 @@ ff_status ff_objective(ff_handle h, const float* A, const float* B, double* psi)
   FF_HIP(hipMemcpyAsync(terms, out, sizeof terms, hipMemcpyDeviceToHost, h->stream));
   int st[4];
   if ((rc = read_status(h, st)) != FF_OK) return rc;
-  if (st[0] != 0) return blame_factor(h, Af, "ff_objective");
+  if (st[0] != 0) return blame_inverse(h, Af, "ff_objective");
   // (1/(N m n)) sum_i tr(B^-1 G_i A^-1 G_i^T) = tr(B^-1 M) / m
   *psi = log(terms[0] / (double)m) + terms[1] / (double)h->n + terms[2] / (double)m;
   return FF_OK;
@@ -1663,11 +1672,9 @@ ff_status ff_quantize(ff_handle h, const float* W, const float* A, const float* 
   int st[4];
   if ((rc = read_status(h, st)) != FF_OK) return rc;
   if (st[0] != 0) {
-    if ((rc = clear_status(h)) != FF_OK) return rc;
-    FF_HIP(hipStreamSynchronize(h->stream));
+    rc = blame_factor(h, [&] { return quant_factor(h, h->A, A != nullptr ? A : h->A.F[cur]); }, "ff_quantize");
     if (h->timing) collect_timing(h);
-    return fail(FF_ERR_NOT_SPD, std::string("factor ") + (st[1] == 1 ? "A" : "B") +
-                                    " not positive definite in ff_quantize");
+    return rc;
   }
   const int64_t tile_floats = (int64_t)q.MT * q.NT * kTileWK * kTileWK;
   FF_HIP(launch_fill_f32((float*)(ws + q.off_racc), tile_floats, 0.0f, h->stream));

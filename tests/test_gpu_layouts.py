@@ -134,3 +134,27 @@ def test_which_factor_is_blamed(gpu, bad):
     want = oracle.objective(_samples(4, m, n).numpy(), A.double().numpy(), B.double().numpy())
     assert abs(psi - want) < 1e-5
     f.close()
+
+
+@pytest.mark.parametrize("bad", ["A", "B", "AB"])
+@pytest.mark.parametrize("m,n", [(300, 150), (64, 1000)])
+def test_which_factor_the_quantiser_blames(gpu, bad, m, n):
+    """As above for the quantiser's two factorisations, which run on the
+    reversed factors: the pivot that fails first in time is B's."""
+    A, B = _spd(n, 1), _spd(m, 2)
+    A2, B2 = A.clone(), B.clone()
+    if "A" in bad:
+        A2[2, 2] = -1.0        # among the last pivots
+    if "B" in bad:
+        B2[m - 1, m - 1] = -1.0   # the first pivot
+    f = ffe.FlipFlop(torch.zeros(1, m, n, device=gpu))
+    W = torch.randn(m, n, generator=torch.Generator().manual_seed(3)).to(gpu)
+    for _ in range(3):
+        with pytest.raises(ffe.FlipFlopError) as e:
+            f.quantize(W, A2.to(gpu), B2.to(gpu), gamma=2.0)
+        assert e.value.code == ffe.FF_ERR_NOT_SPD
+        assert f"factor {bad[0]} not positive definite in ff_quantize" in str(e.value)
+    # and the handle stays usable
+    _, _, alpha, beta, dist = f.quantize(W, A.to(gpu), B.to(gpu), gamma=2.0)
+    assert torch.isfinite(alpha).all() and torch.isfinite(beta).all() and np.isfinite(dist)
+    f.close()
