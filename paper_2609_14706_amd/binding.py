@@ -308,8 +308,9 @@ class FlipFlop:
         cfg.whiten_split = int(whiten_split)
         nbytes = ff_workspace_size(cfg)
         if workspace is not None:
-            if (workspace.device != G.device or workspace.dtype != torch.uint8
-                    or workspace.numel() < nbytes + 256):
+            # ff_init also takes a little less (unpadded factorisations of odd
+            # widths) and says if it does not
+            if (workspace.device != G.device or workspace.dtype != torch.uint8 or workspace.numel() < 257):
                 raise ValueError(f"workspace must be a uint8 tensor of >= {nbytes + 256} bytes on {G.device}")
             self.workspace = workspace
         else:
@@ -317,9 +318,15 @@ class FlipFlop:
                 self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device=G.device)
         base = self.workspace.data_ptr()
         cfg.workspace = (base + 255) // 256 * 256
-        cfg.workspace_bytes = nbytes
+        cfg.workspace_bytes = min(nbytes, self.workspace.numel() - 256)
         self.cfg = cfg
-        self.h = ff_init(cfg)
+        try:
+            self.h = ff_init(cfg)
+        except FlipFlopError as e:
+            if workspace is not None and e.code == FF_ERR_WORKSPACE:
+                raise ValueError(f"workspace must be a uint8 tensor of >= {nbytes + 256} bytes on "
+                                 f"{G.device}") from e
+            raise
         self.iters_done = 0
 
     @staticmethod

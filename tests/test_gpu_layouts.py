@@ -158,3 +158,33 @@ def test_which_factor_the_quantiser_blames(gpu, bad, m, n):
     _, _, alpha, beta, dist = f.quantize(W, A.to(gpu), B.to(gpu), gamma=2.0)
     assert torch.isfinite(alpha).all() and torch.isfinite(beta).all() and np.isfinite(dist)
     f.close()
+
+
+@pytest.mark.parametrize("m,n", [(131, 257), (130, 256)])
+def test_workspace_of_unpadded_factorisations(gpu, m, n):
+    """A workspace without room for padded factorisation rows is taken, by the
+    library and by the class, and gives the same results; less is refused."""
+    G = _samples(20, m, n).to(gpu)
+    full = ffe.FlipFlop.workspace_bytes(m, n, 20, "f32")
+
+    def accepted(size):
+        try:
+            ffe.FlipFlop(G, workspace=torch.empty(size, dtype=torch.uint8, device=gpu)).close()
+            return True
+        except ValueError:
+            return False
+    # L and L^-1 of an odd width d, d x (d + 3) / 4 * 4 floats each, aligned to 256 bytes
+    least = full
+    for d in (m, n):
+        pad = -(-d // 4) * 4
+        least -= 2 * (-(-d * pad * 4 // 256) - -(-d * d * 4 // 256)) * 256
+    assert least < full
+    assert accepted(full) and accepted(least) and not accepted(least - 1) and not accepted(100)
+    out = []
+    for size in (full, least):
+        f = ffe.FlipFlop(G, workspace=torch.empty(size, dtype=torch.uint8, device=gpu))
+        ll = f.iterate(2)
+        out.append((*f.factors(), ll))
+        f.close()
+    # the same steps on rows of other lengths: element loads in place of vectors
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1]) and out[0][2] == out[1][2]
