@@ -56,7 +56,15 @@ typedef enum {
 } ff_status;
 
 /* Element type of the samples G.  The factors are always fp32.
- * FF_F32: every product runs in fp32 (fp32 matrix cores, fp32 accumulate).
+ * FF_F32: every product has fp32 operands and accumulates in fp32.  Small
+ * products run on the fp32 matrix cores.  Large ones run on the bf16 matrix
+ * cores, every operand entry in three bf16 parts that hold all its bits; the
+ * part products below 2^-24 of a product are dropped.  Sums over many terms
+ * come out nearer to the exact ones than with fp32 instructions; a sum that
+ * one term makes up is off by up to 2^-23 of it (2^-22 in sums over more than
+ * 16384 terms), instead of 2^-24.  Entries that three bf16 parts do not hold (the largest, infinite and very small
+ * ones) are multiplied in fp32; subnormal entries below 2^-133 may count as
+ * zeros.
  * FF_BF16: G is bf16; the whitening operand L^-1 and the whitened samples
  * are rounded to bf16 (round to nearest even) and all products accumulate
  * in fp32 on the bf16 matrix cores; factorisations stay in fp32. */
@@ -152,8 +160,12 @@ typedef struct {
                              MARGINAL and INPUT need FF_SAMPLES_RANK1 */
 } ff_config;
 
-/* Bytes of device workspace ff_init needs for cfg (only the shape, dtype and
- * whiten_split fields are read).  Errors: FF_ERR_INVALID_ARG. */
+/* Bytes of device workspace for ff_init with cfg (only the shape, dtype and
+ * whiten_split fields are read).  When m or n is not a multiple of four, the
+ * factorisations' rows are padded to one; ff_init also takes a workspace that
+ * lacks just that room, 2 (m + n) rows of at most three floats, and then
+ * leaves the rows unpadded (the same results, slower factorisations).
+ * Errors: FF_ERR_INVALID_ARG. */
 ff_status ff_workspace_size(const ff_config* cfg, size_t* bytes);
 
 /* Validate cfg, lay out the workspace and enqueue the set-up on cfg->stream:
@@ -225,7 +237,12 @@ ff_status ff_factors(ff_handle h, float* A, float* B, int on_host);
 /* Apply the current Kronecker factors to `batch` matrices X_b (m x n):
  * FF_APPLY: Y_b = B X_b A  (= (A (x) B) vec(X_b), column-major vec);
  * FF_APPLY_INV: Y_b = B^-1 X_b A^-1.  X and Y are DEVICE fp32 [batch][m][n],
- * 16-byte aligned and must not overlap.  Computed in fp32.
+ * 16-byte aligned and must not overlap.  Computed in fp32 as the products of
+ * FF_F32 are.  The size of the batch and of the handle's workspace decide how
+ * many matrices share a launch and with it the kind of product: the same X_b
+ * may get other last bits in another batch (as near to the exact result), the
+ * same call the same bits.  INV factorises A and B side by side, B on a second
+ * stream as ff_quantize does.  Synchronises the stream.
  * Errors: FF_ERR_INVALID_ARG, FF_ERR_NOT_SPD (INV with a singular factor),
  * FF_ERR_HIP. */
 ff_status ff_kron_apply(ff_handle h, const float* X, float* Y, int64_t batch,
@@ -243,7 +260,8 @@ ff_status ff_kron_apply(ff_handle h, const float* X, float* Y, int64_t batch,
  * definite matrices (lower triangles read); either may be NULL to use the
  * handle's current factor.  The trace term runs through the handle's path
  * (bf16 whitening on a bf16 handle), the log-determinants come from its fp32
- * Cholesky factorisations.  Synchronises the stream.  The handle's factors
+ * Cholesky factorisations (side by side, B's on a second stream as in
+ * ff_quantize).  Synchronises the stream.  The handle's factors
  * are untouched; the next ff_iterate refactorises them.
  * Errors: FF_ERR_INVALID_ARG, FF_ERR_NOT_SPD (A or B not positive definite),
  * FF_ERR_HIP. */
@@ -307,9 +325,9 @@ ff_status ff_quantize(ff_handle h, const float* W, const float* A, const float* 
  * array and the set-up rewrites everything it reads, so a call depends on no
  * earlier one; calls that overlap in time on one device (several host
  * threads or streams) race and give undefined results.
- * Errors: FF_ERR_WORKSPACE when ff_workspace_size(cfg) exceeds
- * FF_NOALLOC_SCRATCH_BYTES (the message gives both sizes), and the errors of
- * ff_init and ff_iterate. */
+ * Errors: FF_ERR_WORKSPACE when the least workspace that ff_init takes for cfg
+ * (see ff_workspace_size) exceeds FF_NOALLOC_SCRATCH_BYTES (the message gives
+ * both sizes), and the errors of ff_init and ff_iterate. */
 #define FF_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 ff_status ff_fit_noalloc(const ff_config* cfg, int iters, int* iters_done, double* loglik,
                          float* A, float* B);

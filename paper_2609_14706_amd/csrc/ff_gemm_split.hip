@@ -17,14 +17,18 @@
 // 256 x 128 output tiles, four waves of 128 x 64 (8 x 4 tiles of
 // v_mfma_f32_16x16x32_bf16), one workgroup per CU.  k goes in slices of 32:
 // fp32 from global memory into registers two slices ahead, split one slice
-// ahead, the parts through two LDS buffers (144 KB).  All of it runs in the
-// shadow of the products: within a slice's 192 matrix instructions (16
-// cycles each) every one is followed by a few others (the splitting takes
-// about 340, the LDS reads and writes 54), in a fixed program order.
-// The slice's one barrier comes before its last 34 products, which hide the
-// reads of the next slice's first fragments.  All 512 registers are in use: 0 to
-// 22 values (the loop's operand addresses first) are kept in scratch memory.  Bound by the matrix cores (six
-// products); the LDS moves 216 KB per 3072 cycles.
+// ahead, the parts through two LDS buffers (144 KB).  All of it stands
+// between the products: within a slice's 192 matrix instructions (16 cycles
+// each) every one is followed by a few others (the splitting takes about 340,
+// the LDS reads and writes 54), in a fixed program order.  The slice's one
+// barrier comes before its last 34 products, which hide the reads of the next
+// slice's first fragments.  What bounds it is the instructions that the lone
+// wave of each SIMD can issue: about 590 vector and 54 LDS instructions a slice
+// in some 6000 cycles, the matrix cores busy for half of them (counters, 4096
+// square triangular products at 2.0 GHz, 0.38 to 0.44 ms each), so every further
+// instruction in the loop shows.  256 vector and 256 accumulator registers are
+// in use: 0 to 22 values (the loop's operand addresses first) are kept in
+// scratch memory.
 #include <math.h>
 
 #include <type_traits>
