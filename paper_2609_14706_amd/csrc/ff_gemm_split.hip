@@ -58,7 +58,7 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 // rows, one chunk) cover all banks.
 struct __align__(16) SplitLDS {
   char p[2 * BUF];
-  uint32_t big;  // bits of the largest magnitude of the tile's entries
+  uint32_t big;  // bits of the largest magnitude of the tile's entries (if tiny)
   int tiny;      // set if a nonzero entry is below kTiny
   int wide;      // set if the tile has to be computed from the fp32 numbers
 };
@@ -540,11 +540,12 @@ __global__ __launch_bounds__(256, 1) void k_gemm_split(GemmF32 p, uint32_t gx, u
 #pragma unroll
           for (int j = 0; j < 4; ++j) acc[i][j] += lo[i][j];
       }
-      atomicMax(&sm.big, __float_as_uint(rg.big));
       if (__any(rg.wide())) sm.wide = 1;
       if (__any(rg.tiny())) sm.tiny = 1;
       lds_barrier();
       if (__builtin_amdgcn_readfirstlane(sm.tiny) != 0) {
+        atomicMax(&sm.big, __float_as_uint(rg.big));
+        lds_barrier();
         const float reach = kTinyReach * (float)(khi - klo) * __uint_as_float(sm.big);
         float least = INFINITY;
 #pragma unroll
