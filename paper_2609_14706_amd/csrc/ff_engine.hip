@@ -128,25 +128,23 @@ int choose_splits_f32(int64_t dim_p, int64_t K) {
   int64_t S = std::max<int64_t>(1, 512 / tiles);
   S = std::min<int64_t>(S, std::max<int64_t>(1, K / 256));
   S = std::min<int64_t>(S, 256);
-  auto wide_tiles = [&](int64_t s) {
+  auto route = [&](int64_t s) {
     GemmF32 g{};
     g.M = g.N = dim_p;
     g.K = K;
     g.flags = kCLower;
     g.ksplit = (int)s;
-    return gemm_takes_split(g, 1, true);
+    return gemm_route(g, 1, true);
   };
-  if (!wide_tiles(S)) return (int)S;
-  // 256 x 128 tiles, one workgroup per CU: of the splits up to that many (the
-  // partial outputs' memory), the one with the least rounds of 256 workgroups
-  // times slices of 32 k; 14 -> 12 splits of a 1024-wide product over 32768 k
-  // are one round instead of two
-  int64_t wide = 0, best = INT64_MAX, bestS = S;
-  for (int64_t b = 0; b < (dim_p + 255) / 256; ++b) wide += std::min<int64_t>(2 * (b + 1), T);
-  for (int64_t s = S; s >= 1 && wide_tiles(s); --s) {
-    const int64_t t = (wide * s + 255) / 256 * ((K + 32 * s - 1) / (32 * s) + 4);
-    if (t < best) {
-      best = t;
+  // 256 x 128 tiles, one workgroup per CU, may do better with fewer splits (fewer
+  // rounds of 256 workgroups, which are fuller): 14 -> 12 splits of a 1024-wide
+  // product over 32768 k are one round instead of two
+  GemmRoute best = route(S);
+  int64_t bestS = S;
+  for (int64_t s = S - 1; s >= 1; --s) {
+    const GemmRoute r = route(s);
+    if (r.tile == 256 && r.us < best.us) {
+      best = r;
       bestS = s;
     }
   }

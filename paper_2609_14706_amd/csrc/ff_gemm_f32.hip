@@ -1,10 +1,12 @@
 // General fp32 product on the fp32 matrix cores (v_mfma_f32_32x32x2_f32).
 //
 // The smaller fp32 products: the tree of the triangular inverse of a factor,
-// smaller fp32 layers.  64 x 64 output tiles, four waves of one 32 x 32
-// matrix-core tile, 64-wide k slices staged through double-buffered LDS (such
-// products are latency bound: few, large slices).  Products that fill the GPU
-// with larger tiles go to ff_gemm_split.hip.  Any shape and
+// smaller fp32 layers and Kronecker applications.  64 x 64 output tiles, four
+// waves of one 32 x 32 matrix-core tile, 64-wide k slices staged through
+// double-buffered LDS (such products are latency bound: few, large slices), or,
+// for many products about 128 wide, 128 x 128 tiles, four waves of 2 x 2
+// matrix-core tiles, 32-wide slices; both sum k in the same order.  Products
+// that fill the GPU with larger tiles go to ff_gemm_split.hip.  Any shape and
 // either operand transpose; k ranges can be clipped to the non-zero triangle
 // of a triangular operand, k can run over segments (the stacked samples), and
 // k can be split over the grid into partial outputs.  When every operand is
@@ -21,8 +23,10 @@ namespace {
 // k range per workgroup above which products use two-level accumulation
 constexpr int64_t kDeepK = 16384;
 
-constexpr int BT = 64;  // tile rows and columns
-constexpr int BK = 64;  // k per LDS slice
+// k per LDS slice: 32 for 128 x 128 tiles, 64 for 64 x 64 tiles (the small
+// products of the factorisation are latency bound: fewer, larger slices).
+template <int BT>
+constexpr int slice_k() { return BT == 128 ? 32 : 64; }
 
 // Offset of k in a k axis made of segments of kseg, seg apart (kseg == 0:
 // one contiguous axis, no division).
@@ -30,13 +34,14 @@ __device__ __forceinline__ int64_t seg_off(int64_t k, int64_t kseg, int64_t seg)
   return kseg ? (k / kseg) * seg + (k % kseg) : k;
 }
 
-// One operand slice: 64 "outer" indices (rows of op(A) or columns of op(B))
-// x 64 k.  KMAJ: the operand is contiguous along k (element (o, k) at
+// One operand slice: BT "outer" indices (rows of op(A) or columns of op(B))
+// x BK k.  KMAJ: the operand is contiguous along k (element (o, k) at
 // P[o * ld + koff(k)]); otherwise contiguous along o (at P[koff(k) * ld + o]).
 // Each thread fetches NQ 4-element groups; slice[k][o] is written to LDS.
 // FAST: the whole slice is in bounds and 16-byte vectors can be used.
-template <bool KMAJ, bool FAST>
+template <int BT, bool KMAJ, bool FAST>
 struct SliceLoader {
+  static constexpr int BK = slice_k<BT>();
   static constexpr int NQ = BT * BK / 4 / 256;  // 4-element groups per thread
   static constexpr int OQ = BT / 4;             // 4-element groups per k row (non-k-major)
   f32x4 v[NQ];
@@ -83,23 +88,25 @@ struct SliceLoader {
   }
 };
 
+template <int BT>
 struct TileLDS {
-  float a[2][BK][BT + 4];
-  float b[2][BK][BT + 4];
+  float a[2][slice_k<BT>()][BT + 4];
+  float b[2][slice_k<BT>()][BT + 4];
 };
 
-// acc += op(A)[i0.., klo..khi) op(B)[klo..khi), j0..) for one tile (each wave
-// one 32 x 32 quadrant).
+// acc += op(A)[i0.., klo..khi) op(B)[klo..khi), j0..) for one BT x BT tile
+// (each wave a (BT/2) x (BT/2) quadrant of MT x MT 32 x 32 matrix-core tiles).
 // DEEP: two-level accumulation (see below), for long k ranges only: its
 // second set of accumulators halves the waves a CU can hold.
-template <bool AK, bool BKM, bool FAST, bool DEEP>
+template <int BT, bool AK, bool BKM, bool FAST, bool DEEP>
 __device__ __forceinline__ void tile_product(const GemmF32& p, const float* A, const float* B,
                                              int64_t i0, int64_t j0, int64_t klo, int64_t khi,
-                                             TileLDS& sm, f32x16& acc) {
+                                             TileLDS<BT>& sm, f32x16 (&acc)[BT / 64][BT / 64]) {
+  constexpr int MT = BT / 64, BK = slice_k<BT>();
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1;
-  SliceLoader<AK, FAST> la;
-  SliceLoader<BKM, FAST> lb;
+  SliceLoader<BT, AK, FAST> la;
+  SliceLoader<BT, BKM, FAST> lb;
   la.load(A, p.lda, i0, p.M, klo, khi, p.kseg, p.segA, tid);
   lb.load(B, p.ldb, j0, p.N, klo, khi, p.kseg, p.segB, tid);
   la.store(sm.a[0], tid);
@@ -110,9 +117,13 @@ __device__ __forceinline__ void tile_product(const GemmF32& p, const float* A, c
   // stacked samples, hundreds of thousands deep) thus round each output
   // element about CHUNK * BK / 2 + K / (CHUNK * BK) times instead of K / 2.
   constexpr int CHUNK = 8;
-  f32x16 loc;
+  f32x16 loc[MT][MT];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) loc[r] = 0.0f;
+  for (int a = 0; a < MT; ++a)
+#pragma unroll
+    for (int b = 0; b < MT; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) loc[a][b][r] = 0.0f;
   int cnt = 0;
   int cur = 0;
   for (int64_t k0 = klo; k0 < khi; k0 += BK) {
@@ -123,24 +134,42 @@ __device__ __forceinline__ void tile_product(const GemmF32& p, const float* A, c
     }
     __builtin_amdgcn_sched_barrier(0);
     // operands of k-step s + 1 are read while the products of step s run
-    float fa[2], fb[2];
-    fa[0] = sm.a[cur][lane >> 5][wm * 32 + (lane & 31)];
-    fb[0] = sm.b[cur][lane >> 5][wn * 32 + (lane & 31)];
+    float fa[2][MT], fb[2][MT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      fa[0][t] = sm.a[cur][lane >> 5][wm * (BT / 2) + t * 32 + (lane & 31)];
+      fb[0][t] = sm.b[cur][lane >> 5][wn * (BT / 2) + t * 32 + (lane & 31)];
+    }
 #pragma unroll
     for (int s = 0; s < BK / 2; ++s) {
       if (s + 1 < BK / 2) {
         const int kr = 2 * (s + 1) + (lane >> 5);
-        fa[(s + 1) & 1] = sm.a[cur][kr][wm * 32 + (lane & 31)];
-        fb[(s + 1) & 1] = sm.b[cur][kr][wn * 32 + (lane & 31)];
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+          fa[(s + 1) & 1][t] = sm.a[cur][kr][wm * (BT / 2) + t * 32 + (lane & 31)];
+          fb[(s + 1) & 1][t] = sm.b[cur][kr][wn * (BT / 2) + t * 32 + (lane & 31)];
+        }
       }
       __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the products
-      if constexpr (DEEP) loc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s & 1], fb[s & 1], loc, 0, 0, 0);
-      else acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s & 1], fb[s & 1], acc, 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < MT; ++b) {
+          if constexpr (DEEP)
+            loc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s & 1][a], fb[s & 1][b], loc[a][b], 0, 0, 0);
+          else
+            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s & 1][a], fb[s & 1][b], acc[a][b], 0, 0, 0);
+        }
     }
     if (DEEP && (++cnt == CHUNK || !more)) {
-      acc += loc;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) loc[r] = 0.0f;
+      for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < MT; ++b) {
+          acc[a][b] += loc[a][b];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) loc[a][b][r] = 0.0f;
+        }
       cnt = 0;
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -153,8 +182,9 @@ __device__ __forceinline__ void tile_product(const GemmF32& p, const float* A, c
   }
 }
 
-template <int TA, int TBT, bool VEC, bool DEEP>
+template <int BT, int TA, int TBT, bool VEC, bool DEEP>
 __global__ __launch_bounds__(256) void k_gemm_f32(GemmF32 p) {
+  constexpr int MT = BT / 64, BK = slice_k<BT>();
   if (ff_halted(p.st)) return;
   // With a triangular operand the k range, hence the work, of a tile grows
   // along one tile index: walk the tiles with that index slowest and from the
@@ -189,29 +219,37 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmF32 p) {
     B += (int64_t)blockIdx.z * p.sB;
     C += (int64_t)blockIdx.z * p.sC;
   }
-  __shared__ __align__(16) TileLDS sm;
+  __shared__ __align__(16) TileLDS<BT> sm;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 1, wn = wave & 1;
-  f32x16 acc;
+  f32x16 acc[MT][MT];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+  for (int a = 0; a < MT; ++a)
+#pragma unroll
+    for (int b = 0; b < MT; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
   if (klo < khi) {
     const bool fast = VEC && i0 + BT <= p.M && j0 + BT <= p.N && (khi - klo) % BK == 0;
-    if (fast) tile_product<TA == 0, TBT != 0, VEC, DEEP>(p, A, B, i0, j0, klo, khi, sm, acc);
-    else tile_product<TA == 0, TBT != 0, false, DEEP>(p, A, B, i0, j0, klo, khi, sm, acc);
+    if (fast) tile_product<BT, TA == 0, TBT != 0, VEC, DEEP>(p, A, B, i0, j0, klo, khi, sm, acc);
+    else tile_product<BT, TA == 0, TBT != 0, false, DEEP>(p, A, B, i0, j0, klo, khi, sm, acc);
   }
   const bool lower = (p.flags & kCLower) != 0;
   const bool use_beta = p.ksplit <= 1 && p.beta != 0.0f;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int64_t i = i0 + wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    const int64_t j = j0 + wn * 32 + (lane & 31);
-    if (i < p.M && j < p.N && (!lower || i >= j)) {
-      float v = p.alpha * acc[r];
-      if (use_beta) v += p.beta * C[i * p.ldc + j];
-      C[i * p.ldc + j] = v;
-    }
-  }
+  for (int a = 0; a < MT; ++a)
+#pragma unroll
+    for (int b = 0; b < MT; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int64_t i = i0 + wm * (BT / 2) + a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const int64_t j = j0 + wn * (BT / 2) + b * 32 + (lane & 31);
+        if (i < p.M && j < p.N && (!lower || i >= j)) {
+          float v = p.alpha * acc[a][b][r];
+          if (use_beta) v += p.beta * C[i * p.ldc + j];
+          C[i * p.ldc + j] = v;
+        }
+      }
 }
 
 __global__ __launch_bounds__(256) void k_reduce_rowmajor(const float* __restrict__ P, int splits,
@@ -245,6 +283,7 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 }  // namespace
 
+template <int BT>
 hipError_t launch_tiles(const GemmF32& p, int batch, bool vec, bool deep, hipStream_t s) {
   const int64_t gx = (p.M + BT - 1) / BT, gy = (p.N + BT - 1) / BT;
   const int gz = p.ksplit > 1 ? p.ksplit : batch;
@@ -253,7 +292,7 @@ hipError_t launch_tiles(const GemmF32& p, int batch, bool vec, bool deep, hipStr
   const int sel = (p.transA ? 1 : 0) | (p.transB ? 2 : 0) | (vec ? 4 : 0) | (deep ? 8 : 0);
   switch (sel) {
 #define FF_GEMM_CASE(c, ta, tb, v, dp) \
-    case c: hipLaunchKernelGGL((k_gemm_f32<ta, tb, v, dp>), grid, dim3(256), 0, s, p); break;
+    case c: hipLaunchKernelGGL((k_gemm_f32<BT, ta, tb, v, dp>), grid, dim3(256), 0, s, p); break;
     FF_GEMM_CASE(0, 0, 0, false, false)
     FF_GEMM_CASE(1, 1, 0, false, false)
     FF_GEMM_CASE(2, 0, 1, false, false)
@@ -269,48 +308,65 @@ hipError_t launch_tiles(const GemmF32& p, int batch, bool vec, bool deep, hipStr
     FF_GEMM_CASE(12, 0, 0, true, true)
     FF_GEMM_CASE(13, 1, 0, true, true)
     FF_GEMM_CASE(14, 0, 1, true, true)
-    default: hipLaunchKernelGGL((k_gemm_f32<1, 1, true, true>), grid, dim3(256), 0, s, p); break;
+    default: hipLaunchKernelGGL((k_gemm_f32<BT, 1, 1, true, true>), grid, dim3(256), 0, s, p); break;
 #undef FF_GEMM_CASE
   }
   return hipGetLastError();
 }
 
-// Which route is faster, from the work that the busiest CU gets in each, in
-// units of one k of a 64 x 64 tile (25 ns; 35 where its loads are checked):
-//  * 64 x 64 tiles: one k each, rounds of 256 tiles, triangular ranges evened
-//    out over the rounds;
-//  * 256 x 128 tiles of three-part products: three units a k and about 128 k
-//    to begin and end, rounds of 256 tiles, the first of which has the longest
-//    range.
-// Partly empty tiles and rounds count in full on both sides, so many products
-// smaller than a large tile stay with the small ones.  Measured, us, 64 x 64
-// tiles against 256 x 128: dense 1408 square 71 / 112, 1500 square 175 / 132,
-// 2048 square 194 / 159, 2000 x 3000 618 / 238; eight of 1024 square 196 / 92; 2048
-// of 64 square 24 / 114, 2048 of 16 square 22 / 95, 1024 of 128 square 65 / 84;
-// triangular 2304 square 150 / 174, 2600 square 241 / 205; 65536 whitened rows of
-// 64 14 / 21, of 192 57 / 58, of 256 86 / 67, of 512 273 / 198; symmetric from 65536 k in
-// parts, 192 wide 58 / 85, 256 wide 143 / 87, 1024 wide 1869 / 675.
-bool gemm_takes_split(const GemmF32& p, int batch, bool vec) {
+// Which route is faster, from the work of the busiest CU in each; times in us.
+// A launch goes in rounds of 256 tiles, each as long as the tiles' mean k
+// range, all of them together no shorter than the longest range where tiles are
+// large; a 64 x 64 tile takes 21 ns a k, a 128 x 128 one and a 256 x 128 one of
+// three-part products 70.  What begins and ends a tile counts as so many k, and
+// a product whose loads are checked (tiles that its edges cut, unaligned
+// operands, split k) takes half as long again on the fp32 routes.  The constants
+// fit 122 measured products of 16 to 262144 rows within 10% on average (15% the
+// 128 x 128 tiles); where two routes are close, the split is passed over.  The
+// route taken is the fastest in all but seven of them, 16% slower in the worst.
+// Measured, us, 64 x 64 / 256 x 128 / 128 x 128: dense 1408 square 70 / 112 / 119,
+// 1500 square 174 / 131 / 187, 2048 square 192 / 158 / 171, 2000 x 3000 612 / 236 / 583;
+// eight of 1024 square 195 / 90 / 146; 2048 of 64 square 23 / 101 / 68, 1024 of 128
+// square 65 / 77 / 52; triangular 2304 square 150 / 174 / 216, 2600 square
+// 241 / 205 / 356; 65536 whitened rows of 64 14 / 17 / 23, of 128 31 / 24 / 28, of 256
+// 86 / 60 / 70, of 512 275 / 184 / 205; symmetric from 65536 k in parts, 128 wide
+// 38 / 60 / 33, 192 wide 59 / 79 / 181, 256 wide 142 / 81 / 118, 1024 wide 1888 / 666 / 1427.
+GemmRoute gemm_route(const GemmF32& p, int batch, bool vec) {
   const bool lower = (p.flags & kCLower) != 0;
-  if (p.tile == 64 || (lower && p.M != p.N) || p.lda > kSplitMaxLd || p.ldb > kSplitMaxLd) return false;
-  if (p.M <= 128) return false;  // half of every large tile or more is empty
+  const bool row = (p.flags & (kKHiRow | kKLoRow)) != 0, col = (p.flags & (kKHiCol | kKLoCol)) != 0;
   auto parts = [](int64_t x, int64_t t) { return (x + t - 1) / t; };
   const int64_t z = p.ksplit > 1 ? p.ksplit : batch;
-  const int64_t m64 = parts(p.M, 64), m256 = parts(p.M, 256), n128 = parts(p.N, 128);
-  int64_t small = m64 * parts(p.N, 64), large = m256 * n128;
-  if (lower) {
-    small = m64 * (m64 + 1) / 2;
-    large = 0;
-    for (int64_t b = 1; b <= m256; ++b) large += std::min<int64_t>(2 * b, n128);
-  }
-  const double k = p.ksplit > 1 ? (double)parts(p.K, p.ksplit) : (double)p.K;
-  const bool row = (p.flags & (kKHiRow | kKLoRow)) != 0, col = (p.flags & (kKHiCol | kKLoCol)) != 0;
-  // mean ranges of the tiles
-  const double k_small = row || col ? std::min(k, (k + 64) / 2) : k;
-  const double k_large = row ? std::min(k, (k + 256) / 2) : col ? std::min(k, (k + 128) / 2) : k;
-  const double r_small = (double)parts(small * z, 256), r_large = (double)parts(large * z, 256);
-  const bool whole = vec && p.ksplit <= 1 && p.M % 64 == 0 && p.N % 64 == 0 && p.K % 64 == 0;
-  return r_small * k_small * (whole ? 1.0 : 1.4) > 3.0 * (std::max(k, r_large * k_large) + 128.0 * r_large);
+  const double k = (double)(p.ksplit > 1 ? parts(p.K, p.ksplit) : p.K);
+  struct Work {
+    double rounds, mean;  // rounds of 256 tiles; mean k range
+    bool whole;           // every tile and slice is full and loads vectors
+  };
+  auto work = [&](int64_t tm, int64_t tn, int64_t bk) {
+    const int64_t mt = parts(p.M, tm), nt = parts(p.N, tn);
+    int64_t tiles = mt * nt;
+    if (lower) {  // those that reach the lower triangle
+      tiles = 0;
+      for (int64_t i = 1; i <= mt; ++i) tiles += std::min<int64_t>(parts(std::min(i * tm, p.M), tn), nt);
+    }
+    Work w;
+    w.rounds = (double)parts(tiles * z, 256);
+    w.mean = row ? std::min(k, (k + (double)tm) / 2) : col ? std::min(k, (k + (double)tn) / 2) : k;
+    w.whole = vec && p.ksplit <= 1 && p.M % tm == 0 && p.N % tn == 0 && p.K % bk == 0;
+    return w;
+  };
+  const Work w64 = work(64, 64, 64);
+  GemmRoute best{64, 0.0206 * (w64.rounds * w64.mean + 0.37 * k + 96.0 * w64.rounds) * (w64.whole ? 1.0 : 1.58)};
+  if (p.tile == 64) return best;
+  const Work w128 = work(128, 128, 32);
+  const double t128 = 0.0637 * (std::max(k, w128.rounds * w128.mean) + 0.3 * k + 65.0 * w128.rounds) * (w128.whole ? 1.0 : 1.49);
+  if (p.tile == 128) return GemmRoute{128, t128};
+  if (t128 < best.us) best = GemmRoute{128, t128};
+  // a lower triangle of at most 128 rows fills less than half of its tile
+  const bool takes = p.lda <= kSplitMaxLd && p.ldb <= kSplitMaxLd && (!lower || (p.M == p.N && p.M > 128));
+  if (!takes) return best;
+  const Work wide = work(256, 128, 32);
+  const double split = 0.0709 * (std::max(k, wide.rounds * wide.mean) + 0.03 * k + 192.0 * wide.rounds);
+  return split < best.us ? GemmRoute{256, split} : best;
 }
 
 hipError_t launch_gemm_f32(const GemmF32& p, int batch, hipStream_t s) {
@@ -326,8 +382,11 @@ hipError_t launch_gemm_f32(const GemmF32& p, int batch, hipStream_t s) {
                    (!segmented || (p.kseg % 4 == 0 && p.segA % 4 == 0 && p.segB % 4 == 0));
   GemmF32 q = p;
   if (!segmented) q.kseg = 0;  // plain k axis: the kernels skip the segment arithmetic
-  if (gemm_takes_split(p, batch, vec)) return launch_gemm_split(q, batch, vec, deep, s);
-  return launch_tiles(q, batch, vec, deep, s);
+  switch (gemm_route(p, batch, vec).tile) {
+    case 256: return launch_gemm_split(q, batch, vec, deep, s);
+    case 128: return launch_tiles<128>(q, batch, vec, deep, s);
+    default: return launch_tiles<64>(q, batch, vec, deep, s);
+  }
 }
 
 hipError_t launch_reduce_rowmajor(const float* P, int splits, int64_t dim_p, float* F,

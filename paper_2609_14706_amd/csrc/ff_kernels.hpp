@@ -75,10 +75,10 @@ struct GemmF32 {
   int64_t segA, segB;
   int ksplit;          // > 1: grid z splits k, C += z * sC, beta ignored
   const int* st;
-  int tile;            // 0: chosen by size; 64: 64 x 64 tiles
+  int tile;            // 0: chosen by size (gemm_route); 64, 128: tiles of that size
 };
-// C = alpha * op(A) op(B) + beta * C: on the fp32 matrix cores in 64 x 64
-// tiles, or with launch_gemm_split where that is faster (gemm_takes_split).
+// C = alpha * op(A) op(B) + beta * C: on the fp32 matrix cores in 64 x 64 or
+// 128 x 128 tiles, or with launch_gemm_split, whichever is fastest (gemm_route).
 hipError_t launch_gemm_f32(const GemmF32& p, int batch, hipStream_t s);
 // The same on the bf16 matrix cores, every fp32 entry split into three bf16
 // parts; 256 x 128 tiles (ff_gemm_split.hip).  kseg = 0: plain k axis.  vec:
@@ -87,9 +87,14 @@ hipError_t launch_gemm_f32(const GemmF32& p, int batch, hipStream_t s);
 // lda, ldb <= kSplitMaxLd (32-bit offsets within a tile's slice).
 constexpr int64_t kSplitMaxLd = 1 << 23;
 hipError_t launch_gemm_split(const GemmF32& p, int batch, bool vec, bool deep, hipStream_t s);
-// Whether launch_gemm_f32 takes it (from the sizes, flags, ksplit, tile, lda
-// and ldb of p alone).
-bool gemm_takes_split(const GemmF32& p, int batch, bool vec);
+// The route of launch_gemm_f32: 64 or 128 (square tiles) or 256
+// (launch_gemm_split), and its expected time (from the sizes, flags, ksplit,
+// tile, lda and ldb of p alone).
+struct GemmRoute {
+  int tile;
+  double us;
+};
+GemmRoute gemm_route(const GemmF32& p, int batch, bool vec);
 
 // F (dim x dim) = scale * sum_z P[z] with P[z] row-major dim_p x dim_p, lower
 // triangle read, mirrored.
