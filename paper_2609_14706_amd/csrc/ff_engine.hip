@@ -136,12 +136,16 @@ int choose_splits_f32(int64_t dim_p, int64_t K) {
     g.ksplit = (int)s;
     return gemm_route(g, 1, true);
   };
-  // 256 x 128 tiles, one workgroup per CU, may do better with fewer splits (fewer
-  // rounds of 256 workgroups, which are fuller): 14 -> 12 splits of a 1024-wide
-  // product over 32768 k are one round instead of two
+  // 256 x 128 tiles, one workgroup per CU, may do better with fewer splits: the
+  // most that make whole rounds of 256 workgroups (14 -> 12 splits of a
+  // 1024-wide product over 32768 k are one round instead of two)
+  int64_t wide = 0;
+  for (int64_t b = 0; b < (dim_p + 255) / 256; ++b) wide += std::min<int64_t>(2 * (b + 1), T);
   GemmRoute best = route(S);
   int64_t bestS = S;
-  for (int64_t s = S - 1; s >= 1; --s) {
+  for (int64_t rounds = 1; 256 * rounds / wide < S; ++rounds) {
+    const int64_t s = 256 * rounds / wide;
+    if (s < 1) continue;
     const GemmRoute r = route(s);
     if (r.tile == 256 && r.us < best.us) {
       best = r;

@@ -27,7 +27,7 @@
 // in some 6000 cycles, the matrix cores busy for half of them (counters, 4096
 // square triangular products at 2.0 GHz, 0.38 to 0.44 ms each), so every further
 // instruction in the loop shows.  256 vector and 256 accumulator registers are
-// in use: 0 to 22 values (the loop's operand addresses first) are kept in
+// in use: 0 to 21 values (the loop's operand addresses first) are kept in
 // scratch memory.
 #include <math.h>
 
